@@ -8,10 +8,6 @@
 namespace mg {
 const char *last_error_cstr();
 
-static void pick_tile(const int L[4], int b[4]) {
-  for (int mu = 0; mu < 4; ++mu) b[mu] = (L[mu] % 4 == 0) ? 4 : ((L[mu] % 2 == 0) ? 2 : 1);
-}
-
 int check_lattice(const mg_lattice_t *lat) {
   if (!lat) { set_error("lattice is NULL"); return MG_EINVAL; }
   uint64_t V = 1;
@@ -23,73 +19,41 @@ int check_lattice(const mg_lattice_t *lat) {
   return MG_OK;
 }
 
-template <typename T>
-static int wilson_apply_t(const mg_lattice_t *lat, const void *U, double mass, const void *in, void *out,
-                          int nrhs, hipStream_t st) {
-  int b[4];
-  pick_tile(lat->L, b);
-  Geom g = make_geom(lat->L, b, lat->t_antiperiodic ? 1 : 0);
-  using C = c_t<T>;
-  C *Ui = nullptr, *xi = nullptr, *yi = nullptr;
-  const size_t Vp = g.Vpad;
-  MG_HIP(hipMallocAsync((void **)&Ui, sizeof(C) * 36 * Vp, st));
-  hipError_t e = hipMallocAsync((void **)&xi, sizeof(C) * 12 * Vp * nrhs, st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&yi, sizeof(C) * 12 * Vp * nrhs, st);
-  if (e == hipSuccess) e = pack_gauge<T>(g, (const double2 *)U, Ui, st);
-  if (e == hipSuccess) e = pack_field<T>(g, (const double2 *)in, xi, 12, nrhs, st);
-  if (e == hipSuccess) e = dslash<T>(g, Ui, 9, xi, yi, nullptr, 4.0 + mass, nrhs, DS_PLAIN, nullptr, st);
-  if (e == hipSuccess) e = unpack_field<T>(g, yi, (double2 *)out, 12, nrhs, st);
-  if (yi) (void)hipFreeAsync(yi, st);
-  if (xi) (void)hipFreeAsync(xi, st);
-  (void)hipFreeAsync(Ui, st);
-  if (e != hipSuccess) {
-    set_error(hip_error_string(e, "wilson_apply"));
-    return MG_EHIP;
-  }
-  return MG_OK;
+// Whether the nrhs output spinors share memory with the links or the input
+// (the stencil reads neighbours that the output would have replaced).
+static bool out_overlaps(size_t V, const void *U, const void *in, const void *out, int nrhs) {
+  const uintptr_t o = (uintptr_t)out, no = 192 * V * (size_t)nrhs, i = (uintptr_t)in, u = (uintptr_t)U;
+  return (o < i + no && i < o + no) || (o < u + 576 * V && u < o + no);
+}
+static size_t volume(const mg_lattice_t *lat) {
+  return (size_t)lat->L[0] * lat->L[1] * lat->L[2] * lat->L[3];
 }
 
-// FP16 class: links and spinors stored in binary16 (spinors with a per-site
-// scale), FP32 arithmetic; the complex128 input is rounded to FP32 and then
-// to binary16, and the output widened back.
-static int wilson_apply_f16(const mg_lattice_t *lat, const void *U, double mass, const void *in, void *out,
-                            int nrhs, hipStream_t st) {
-  int b[4];
-  pick_tile(lat->L, b);
-  Geom g = make_geom(lat->L, b, lat->t_antiperiodic ? 1 : 0);
-  const size_t Vp = g.Vpad;
-  double2 *U64 = nullptr, *f64 = nullptr;
-  chalf *Uh = nullptr;
-  h16 *xh = nullptr, *yh = nullptr;
-  hipError_t e = hipMallocAsync((void **)&U64, sizeof(double2) * 36 * Vp, st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&f64, sizeof(double2) * 12 * Vp * nrhs, st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&Uh, sizeof(chalf) * 36 * Vp, st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&xh, sizeof(h16) * 13 * Vp * nrhs, st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&yh, sizeof(h16) * 13 * Vp * nrhs, st);
-  if (e == hipSuccess) e = pack_gauge<double>(g, (const double2 *)U, U64, st);
-  if (e == hipSuccess) e = store_convert<chalf>(Uh, U64, 36 * Vp, st);
-  if (e == hipSuccess) e = pack_field<double>(g, (const double2 *)in, f64, 12, nrhs, st);
-  if (e == hipSuccess) e = to_h16<double2>(xh, f64, (uint32_t)Vp, nrhs, st);
+// out = D in; an output that shares memory with an input is formed in tmp
+// (when it is given) or in a buffer of its own and copied.
+static int wilson_apply_on(const mg_lattice_t *lat, const void *U, double mass, const void *in, void *out, int nrhs,
+                           mg_prec_t prec, void *tmp, hipStream_t st, const char *who) {
+  const size_t V = volume(lat);
+  const bool via = out_overlaps(V, U, in, out, nrhs);
+  double2 *y = (double2 *)(via ? tmp : out);
+  hipError_t e = hipSuccess;
+  if (!y) e = hipMallocAsync((void **)&y, 192 * V * nrhs, st);
   if (e == hipSuccess)
-    e = dslash<float, chalf, h16, h16>(g, Uh, 9, xh, yh, nullptr, 4.0 + mass, nrhs, DS_PLAIN, nullptr, st);
-  if (e == hipSuccess) e = from_h16<double2>(f64, yh, (uint32_t)Vp, nrhs, st);
-  if (e == hipSuccess) e = unpack_field<double>(g, f64, (double2 *)out, 12, nrhs, st);
-  if (yh) (void)hipFreeAsync(yh, st);
-  if (xh) (void)hipFreeAsync(xh, st);
-  if (Uh) (void)hipFreeAsync(Uh, st);
-  if (f64) (void)hipFreeAsync(f64, st);
-  if (U64) (void)hipFreeAsync(U64, st);
+    e = dslash_canon(lat->L, lat->t_antiperiodic ? 1 : 0, (const double2 *)U, mass, (const double2 *)in, y, nrhs, prec,
+                     st);
+  if (e == hipSuccess && via) e = hipMemcpyAsync(out, y, 192 * V * nrhs, hipMemcpyDeviceToDevice, st);
+  if (via && !tmp && y) (void)hipFreeAsync(y, st);
   if (e != hipSuccess) {
-    set_error(hip_error_string(e, "wilson_apply"));
+    set_error(hip_error_string(e, who));
     return MG_EHIP;
   }
   return MG_OK;
 }
 
 // ---------------------------------------------------------------- no-alloc
-// Scratch of wilson_apply_noalloc: the internal link and spinor layouts of
-// one call, in a file-scope device array that each GPU the library runs on
-// holds until the process ends.  Host code never uses the array's name as an
+// Scratch of wilson_apply_noalloc, for an output that shares memory with an
+// input: a file-scope device array that each GPU the library runs on holds
+// until the process ends.  Host code never uses the array's name as an
 // address: it takes the per-device address from hipGetSymbolAddress once per
 // device (on the first call with that device current) and passes that.
 static __device__ __align__(256) unsigned char scratch[MG_NOALLOC_BYTES];
@@ -115,15 +79,12 @@ static int noalloc_scratch(unsigned char **out) {
   return MG_OK;
 }
 
-template <typename T>
-static int wilson_apply_noalloc_t(const mg_lattice_t *lat, const void *U, double mass, const void *in, void *out,
-                                  int nrhs, hipStream_t st) {
-  int b[4];
-  pick_tile(lat->L, b);
-  Geom g = make_geom(lat->L, b, lat->t_antiperiodic ? 1 : 0);
-  using C = c_t<T>;
-  const size_t Vp = g.Vpad;
-  const size_t need = sizeof(C) * (36 + 24 * (size_t)nrhs) * Vp;  // links, in, out
+static int wilson_apply_noalloc_on(const mg_lattice_t *lat, const void *U, double mass, const void *in, void *out,
+                                   int nrhs, mg_prec_t prec, hipStream_t st) {
+  // the entry point's documented limit: links, input and output in the
+  // arithmetic type, the volume rounded up to whole 64-site tiles
+  const size_t Vp = (volume(lat) + 63) / 64 * 64;
+  const size_t need = (prec == MG_F64 ? 16 : 8) * (36 + 24 * (size_t)nrhs) * Vp;
   if (need > (size_t)MG_NOALLOC_BYTES) {
     char buf[256];
     std::snprintf(buf, sizeof(buf),
@@ -134,18 +95,7 @@ static int wilson_apply_noalloc_t(const mg_lattice_t *lat, const void *U, double
   }
   unsigned char *base = nullptr;
   MG_TRY(noalloc_scratch(&base));
-  C *Ui = reinterpret_cast<C *>(base);
-  C *xi = Ui + 36 * Vp;
-  C *yi = xi + 12 * Vp * (size_t)nrhs;
-  hipError_t e = pack_gauge<T>(g, (const double2 *)U, Ui, st);
-  if (e == hipSuccess) e = pack_field<T>(g, (const double2 *)in, xi, 12, nrhs, st);
-  if (e == hipSuccess) e = dslash<T>(g, Ui, 9, xi, yi, nullptr, 4.0 + mass, nrhs, DS_PLAIN, nullptr, st);
-  if (e == hipSuccess) e = unpack_field<T>(g, yi, (double2 *)out, 12, nrhs, st);
-  if (e != hipSuccess) {
-    set_error(hip_error_string(e, "wilson_apply_noalloc"));
-    return MG_EHIP;
-  }
-  return MG_OK;
+  return wilson_apply_on(lat, U, mass, in, out, nrhs, prec, base, st, "wilson_apply_noalloc");
 }
 
 }  // namespace mg
@@ -159,8 +109,7 @@ extern "C" int wilson_apply_noalloc(const mg_lattice_t *lat, const void *U, doub
   if (!U || !in || !out) { set_error("wilson_apply_noalloc: NULL buffer"); return MG_EINVAL; }
   if (in == out) { set_error("wilson_apply_noalloc: in and out alias"); return MG_EINVAL; }
   if (nrhs < 1 || nrhs > 65535) { set_error("wilson_apply_noalloc: nrhs out of range"); return MG_EINVAL; }
-  if (prec == MG_F64) return wilson_apply_noalloc_t<double>(lat, U, mass, in, out, nrhs, stream);
-  if (prec == MG_F32) return wilson_apply_noalloc_t<float>(lat, U, mass, in, out, nrhs, stream);
+  if (prec == MG_F64 || prec == MG_F32) return wilson_apply_noalloc_on(lat, U, mass, in, out, nrhs, prec, stream);
   set_error("wilson_apply_noalloc: precision must be MG_F64 or MG_F32");
   return MG_ENOTSUP;
 }
@@ -172,9 +121,8 @@ extern "C" int wilson_apply(const mg_lattice_t *lat, const void *U, double mass,
   if (!U || !in || !out) { set_error("wilson_apply: NULL buffer"); return MG_EINVAL; }
   if (in == out) { set_error("wilson_apply: in and out alias"); return MG_EINVAL; }
   if (nrhs < 1 || nrhs > 65535) { set_error("wilson_apply: nrhs out of range"); return MG_EINVAL; }
-  if (prec == MG_F64) return wilson_apply_t<double>(lat, U, mass, in, out, nrhs, stream);
-  if (prec == MG_F32) return wilson_apply_t<float>(lat, U, mass, in, out, nrhs, stream);
-  if (prec == MG_F16) return wilson_apply_f16(lat, U, mass, in, out, nrhs, stream);
+  if (prec == MG_F64 || prec == MG_F32 || prec == MG_F16)
+    return wilson_apply_on(lat, U, mass, in, out, nrhs, prec, nullptr, stream, "wilson_apply");
   set_error("wilson_apply: precision must be MG_F64, MG_F32 or MG_F16");
   return MG_ENOTSUP;
 }

@@ -47,6 +47,12 @@ hipError_t dslash(const Geom &g, const S *U, int nl, const TI *in, TO *out, cons
 // out = D in (DS_PLAIN) in FP64 arithmetic on FP32-stored input spinors
 hipError_t dslash_in32(const Geom &g, const double2 *U, int nl, const float2 *in, double2 *out, double diag,
                        int nrhs, hipStream_t st);
+// ---- dslash_canon.hip: out = D in (Eq. 2) on canonical arrays (U[4][site][3][3],
+// nrhs spinors [site][12], lexicographic sites), out apart from U and in.
+// prec: arithmetic as of the internal stencil's classes (MG_F16: links and
+// spinors rounded to binary16 storage on the way in and out).
+hipError_t dslash_canon(const int L[4], int antiperiodic, const double2 *U, double mass, const double2 *in,
+                        double2 *out, int nrhs, mg_prec_t prec, hipStream_t st);
 // Uc = first two rows of every link of U (full FP64 links) in storage type S;
 // blockmax[blk] = max |row2 - conj(row0 x row1)| (dslash_blocks(g) entries).
 template <typename S>
