@@ -625,267 +625,217 @@ template hipError_t cgnr_persistent<float2>(const Geom &, int, const float2 *, c
 // ------------------------------------------------------------ matrix cores
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-template <typename S> __device__ __forceinline__ float2 op_f32(const S &v) { return cvt<float2>(v); }
-
-// Four consecutive operator entries (16-byte aligned) as FP32 complex.
-__device__ __forceinline__ void load4_op(const chalf *p, float2 (&o)[4]) {
-  const chalf4 v = *reinterpret_cast<const chalf4 *>(p);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) o[q] = cvt<float2>(v.v[q]);
-}
-__device__ __forceinline__ void load4_op(const float2 *p, float2 (&o)[4]) {
-  const float4 a = reinterpret_cast<const float4 *>(p)[0], b = reinterpret_cast<const float4 *>(p)[1];
-  o[0] = make_float2(a.x, a.y);
-  o[1] = make_float2(a.z, a.w);
-  o[2] = make_float2(b.x, b.y);
-  o[3] = make_float2(b.z, b.w);
-}
+// Four consecutive operator entries (16-byte aligned) in their storage type.
+template <typename S> struct Op4;
+template <> struct Op4<chalf> {
+  chalf4 v;
+  __device__ __forceinline__ void load(const chalf *p) { v = *reinterpret_cast<const chalf4 *>(p); }
+  __device__ __forceinline__ void set(int q, chalf e) { v.v[q] = e; }
+  __device__ __forceinline__ float2 get(int q) const { return cvt<float2>(v.v[q]); }
+};
+template <> struct Op4<float2> {
+  float2 v[4];
+  __device__ __forceinline__ void load(const float2 *p) {
+    const float4 a = reinterpret_cast<const float4 *>(p)[0], b = reinterpret_cast<const float4 *>(p)[1];
+    v[0] = make_float2(a.x, a.y);
+    v[1] = make_float2(a.z, a.w);
+    v[2] = make_float2(b.x, b.y);
+    v[3] = make_float2(b.z, b.w);
+  }
+  __device__ __forceinline__ void set(int q, float2 e) { v[q] = e; }
+  __device__ __forceinline__ float2 get(int q) const { return v[q]; }
+};
 
 constexpr int MMA_NR = 16;  // right-hand sides per GEMM tile (N of the MFMA)
-constexpr int MMA_U = 8;    // operator k-steps per load batch
 
-// Sums of nr partial vectors (np entries each) over the workgroup, all in one
-// pass; results in every thread.
-__device__ __forceinline__ void block_allsum_multi(const double *__restrict__ p, int np, int nr,
-                                                   double (&out)[MMA_NR], double (*lds)[MMA_NR]) {
-#pragma unroll
-  for (int r = 0; r < MMA_NR; ++r) out[r] = 0.0;
-  for (int i = threadIdx.x; i < np; i += blockDim.x) {
-#pragma unroll
-    for (int r = 0; r < MMA_NR; ++r)
-      if (r < nr) out[r] += p[(size_t)r * np + i];
-  }
-  const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-#pragma unroll
-  for (int r = 0; r < MMA_NR; ++r) out[r] = wave_sum(out[r]);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int r = 0; r < MMA_NR; ++r) lds[w][r] = out[r];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < MMA_NR; ++r) {
-    double t = 0.0;
-    for (int q = 0; q < nw; ++q) t += lds[q][r];
-    out[r] = t;
-  }
-  __syncthreads();
-}
-
-// One workgroup per coarse site, MT = ceil(n / 16) row tiles times KS groups
-// of the K range: wavefront (mt, ks) accumulates rows 16 mt .. 16 mt + 15 of
-// all right-hand sides over the k-steps ks, ks + KS, ... (4 of the 9n
-// (slot, column) pairs per step).  MFMA lane layouts (16x16x4, FP32):
-// A lane l = (row l % 16, k l / 16); B lane l = (k l / 16, column l % 16);
-// C lane l = (rows 4 (l / 16) + 0..3, column l % 16).
-template <typename S, int KS, bool RM>
-__global__ __launch_bounds__(1024) void k_coarse_mma(Geom g, int n, const S *__restrict__ L,
-                                                     const float2 *__restrict__ in, float2 *__restrict__ out,
-                                                     int nrhs, int dagger, double *__restrict__ part, int pw,
-                                                     const int *__restrict__ done, CgCheck chk) {
-  extern __shared__ float2 bl[];  // staged inputs [9n][nrhs]; reused for the K-split reduction
-  __shared__ double wred[16][MMA_NR];
-  __shared__ double pr[4][64][3];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// One workgroup per coarse site.  Every wavefront accumulates all MT =
+// ceil(n / 16) row tiles of all right-hand sides over its share of the K
+// range: blocks of 16 of the 9n (slot, column) pairs, block b to wavefront b
+// mod nw.  MFMA lane layouts (16x16x4, FP32): A lane l = (row l % 16, k l /
+// 16); B lane l = (k l / 16, column l % 16); C lane l = (rows 4 (l / 16) +
+// 0..3, column l % 16).
+//
+// What it is bound by: the matrix cores and the operator's bytes come to
+// about the same time (24^3 x 48, n = 48, 12 right-hand sides, binary16: 34
+// us of MFMA, 215 MB), so nothing else may sit in the loop.  With one row
+// tile per wavefront and range checks on every operand it issued twelve
+// vector instructions per MFMA, 49 us of vector work, 127 us in all.  Here an
+// input entry is read (and its Gauss sum formed) once for all row tiles, and
+// no operand is checked: rows past n repeat row n - 1 and columns past nrhs
+// column 0, whose results are not stored, and the inputs past K are zero.
+// 127 -> 76 us there; FP32 storage 127 -> 101 us, and on level 1 of 32^3 x 64
+// 0.367 -> 0.310 ms (1.4 GB of operator and vectors, 4.5 TB/s).
+template <typename S, int MT, bool RM>
+__global__ __launch_bounds__(512) void k_coarse_mma(Geom g, int n, const S *__restrict__ L,
+                                                    const float2 *__restrict__ in, float2 *__restrict__ out,
+                                                    int nrhs, int dagger, double *__restrict__ part, int pw,
+                                                    const int *__restrict__ done, CgCheck chk) {
+  extern __shared__ __align__(16) float2 bl[];  // staged inputs [16 KB][nrhs | 1], then the wavefronts' sums
+  __shared__ double rsum[MMA_NR];
+  __shared__ double pr[MT][64][3];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
   if (done != nullptr) {
-    bool all = true;
-    for (int r = 0; r < nrhs; ++r) all = all && done[r] != 0;
-    if (all) return;
+    const int d = lane < nrhs ? done[lane] : 1;
+    if (__all(d != 0)) return;
   }
   if (chk.part_r != nullptr) {
-    double rr[MMA_NR];
-    block_allsum_multi(chk.part_r, chk.np_r, nrhs, rr, wred);
-    bool allconv = true;
-    for (int r = 0; r < nrhs; ++r) {
-      if (chk.done[r]) continue;
-      const double *cg = chk.cg + (size_t)r * CG_NS;
-      const int iter = chk.it_in[r];
-      const bool conv = !(rr[r] > cg[4] * cg[3]) || iter + 1 >= chk.maxit;
-      if (blockIdx.x == 0 && tid == 0) {
-        chk.it_out[r] = iter + 1;
-        if (conv) chk.done[r] = 1;
-      }
-      allconv = allconv && conv;
+    // ||r||^2 of right-hand side r by wavefront r mod nw, then lane r of every
+    // wavefront tests right-hand side r (one after another, their loads alone
+    // took a round trip each)
+    for (int r = wv; r < nrhs; r += nw) {
+      double t = 0.0;
+      for (int i = lane; i < chk.np_r; i += 64) t += chk.part_r[(size_t)r * chk.np_r + i];
+      t = wave_sum(t);
+      if (lane == 0) rsum[r] = t;
     }
-    if (allconv) return;
+    const int r = min(lane, nrhs - 1);
+    const double *cg = chk.cg + (size_t)r * CG_NS;
+    const double lim = cg[4] * cg[3];
+    const int was = chk.done[r], iter = chk.it_in[r];
+    __syncthreads();
+    const bool conv = was != 0 || !(rsum[r] > lim) || iter + 1 >= chk.maxit;
+    if (blockIdx.x == 0 && wv == 0 && lane < nrhs && was == 0) {
+      chk.it_out[r] = iter + 1;
+      if (conv) chk.done[r] = 1;
+    }
+    if (__all(conv)) return;
   }
   const uint32_t s = xcd_remap(blockIdx.x, gridDim.x);
-  const int K = 9 * n, half = n >> 1;
-  const int MT = (n + 15) >> 4;
-  const int mt = wv % MT, ks = wv / MT;
-  const int arow = mt * 16 + (lane & 15), kq = lane >> 4, col = lane & 15;
-  const bool arow_ok = arow < n, col_ok = col < nrhs;
-  const int colc = col_ok ? col : 0;
-  // Operator loads are unconditional (indices clamped into the site's block,
-  // out-of-range values zeroed afterwards) and double-buffered MMA_U k-steps
-  // ahead, so every wavefront keeps MMA_U loads in flight; the first batch is
-  // issued before the input staging.
-  // Column-major operator (RM false): lane (row, kq) reads entry (row, k)
-  // of each k-step, rows contiguous.  Row-major copy (RM true): lane (row,
-  // kq) reads the four consecutive columns 16 b + 4 kq .. + 3 of its row in
-  // one access for the four k-steps of block b (k-slot kq of step u takes
-  // column 16 b + 4 kq + u; the sum over K does not depend on term order).
-  const S *La = RM ? L + (size_t)s * K * n + (size_t)(arow_ok ? arow : 0) * K
-                   : L + (size_t)s * K * n + (arow_ok ? arow : 0);
-  const int KQ = (K + 3) >> 2;
-  const int nq = RM ? 0 : (KQ - ks + KS - 1) / KS;  // k-steps of this wavefront
-  const int KB = (K + 15) >> 4;
-  const int nbk = RM ? (ks < KB ? (KB - ks + KS - 1) / KS : 0) : 0;  // k-blocks of this wavefront
-  float2 abuf[2][MMA_U];
-  auto load_batch = [&](float2 (&dst)[MMA_U], int q0) {
+  const int K = 9 * n, half = n >> 1, KB = (K + 15) >> 4, ldb = nrhs | 1;
+  const int kq = lane >> 4, col = lane & 15;
+  const int colc = col < nrhs ? col : 0;
+  // Column-major operator (RM false): lane (row, kq) takes column 16 b + 4 u +
+  // kq of its row in k-step u, rows contiguous.  Row-major copy (RM true): the
+  // four consecutive columns 16 b + 4 kq .. + 3 in one access, column 16 b + 4
+  // kq + u in k-step u (the sum over K does not depend on the order).
+  const S *La[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int row = min(16 * m + (lane & 15), n - 1);
+    La[m] = L + (size_t)s * K * n + (RM ? (size_t)row * K : (size_t)row);
+  }
+  Op4<S> abuf[2][MT];
+  auto load_block = [&](Op4<S> (&dst)[MT], int b) {
     if constexpr (RM) {
+      const int k0 = min(16 * b + 4 * kq, K - 4);
 #pragma unroll
-      for (int u = 0; u < MMA_U / 4; ++u) {
-        const int k0 = min(16 * (ks + min(q0 + u, nbk - 1) * KS) + 4 * kq, K - 4);
-        float2 o[4];
-        load4_op(La + k0, o);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) dst[4 * u + q] = o[q];
-      }
+      for (int m = 0; m < MT; ++m) dst[m].load(La[m] + k0);
     } else {
 #pragma unroll
-      for (int u = 0; u < MMA_U; ++u) {
-        const int kk = min(4 * (ks + (q0 + u) * KS) + kq, K - 1);
-        dst[u] = op_f32(La[(size_t)kk * n]);
+      for (int u = 0; u < 4; ++u) {
+        const size_t o = (size_t)min(16 * b + 4 * u + kq, K - 1) * n;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) dst[m].set(u, La[m][o]);
       }
     }
   };
-  if (RM ? nbk > 0 : true) load_batch(abuf[0], 0);
-  __shared__ uint32_t nbs[9];
-  if (tid < 9) nbs[tid] = slot_site(g, s, tid);
-  __syncthreads();
+  // the first blocks are under way before the inputs are staged
+  if (wv < KB) load_block(abuf[0], wv);
+  if (wv + nw < KB) load_block(abuf[1], wv + nw);
   {
-    // A thread stages 9 nrhs / (blockDim / n) entries (up to 36): SU of
-    // them are loaded before any is stored, so that their round trips
-    // overlap instead of one load, wait and store after another (the
-    // 12-RHS level-1 stencil of 32^3 x 64: 0.400 -> 0.366 ms with SU = 8;
-    // 0.373 with 4, 0.369 with 16).
-    constexpr int SU = 8;
-    const int jj = tid % n, tstep = (int)blockDim.x / n, nt = 9 * nrhs;
-    const bool stager = tid < tstep * n;
-    for (int t0 = tid / n; stager && t0 < nt; t0 += SU * tstep) {
+    // Input block (slot, right-hand side) t to wavefront t mod nw, lanes along
+    // the components: the addresses are scalar but for the lane's part.  SU
+    // entries are loaded before any is stored, so that their round trips
+    // overlap.
+    constexpr int SU = 9;
+    const uint32_t nb = slot_site(g, s, lane < 9 ? lane : 0);
+    const int nt = 9 * nrhs, inv = (65536 + nrhs - 1) / nrhs;  // t / nrhs = t inv >> 16 for t < 9 * 16
+    const int j = lane < n ? lane : n - 1;
+    const bool neg = dagger && j >= half;
+    for (int t0 = __builtin_amdgcn_readfirstlane(wv); t0 < nt; t0 += SU * nw) {
       float2 v[SU];
 #pragma unroll
       for (int u = 0; u < SU; ++u) {
-        const int t = t0 + u * tstep;
-        if (t < nt) v[u] = in[((size_t)(t % nrhs) * g.V + nbs[t / nrhs]) * n + jj];
+        const int t = min(t0 + u * nw, nt - 1), slot = t * inv >> 16;
+        const uint32_t sn = __builtin_amdgcn_readlane(nb, slot);
+        v[u] = in[((size_t)(t - slot * nrhs) * g.V + sn) * n + j];
       }
 #pragma unroll
       for (int u = 0; u < SU; ++u) {
-        const int t = t0 + u * tstep;
-        if (t < nt) {
-          const float2 w = (dagger && jj >= half) ? make_float2(-v[u].x, -v[u].y) : v[u];
-          bl[((t / nrhs) * n + jj) * nrhs + (t % nrhs)] = w;
-        }
+        const int t = min(t0 + u * nw, nt - 1), slot = t * inv >> 16;
+        bl[(slot * n + j) * ldb + (t - slot * nrhs)] = neg ? make_float2(-v[u].x, -v[u].y) : v[u];
       }
     }
+    for (int i = K * ldb + tid; i < KB * 16 * ldb; i += blockDim.x) bl[i] = make_float2(0.f, 0.f);
   }
   __syncthreads();
   // Complex products with three real MFMAs each (Gauss): cre = sum a.x b.x,
   // c2 = sum a.y b.y, cim = sum (a.x + a.y)(b.x + b.y); then re = cre - c2
   // and im = cim - cre - c2.
-  floatx4 cre = {0.f, 0.f, 0.f, 0.f}, cim = {0.f, 0.f, 0.f, 0.f}, c2 = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (RM) {
-    constexpr int BB = MMA_U / 4;  // k-blocks per load batch
-    for (int b0 = 0; b0 < nbk; b0 += 2 * BB) {
+  floatx4 cre[MT], cim[MT], c2[MT];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int bb = b0 + h * BB;
-        if (bb >= nbk) break;
-        if (bb + BB < nbk) load_batch(abuf[h ^ 1], bb + BB);
-#pragma unroll
-        for (int u = 0; u < BB; ++u) {
-          const bool bok = bb + u < nbk;
-          const int kbase = 16 * (ks + (bb + u) * KS) + 4 * kq;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int kk = kbase + q;
-            const bool kok = bok && kk < K;
-            const float2 a = (kok && arow_ok) ? abuf[h][4 * u + q] : make_float2(0.f, 0.f);
-            const float2 bv = bl[min(kk, K - 1) * nrhs + colc];
-            const float2 b = (kok && col_ok) ? bv : make_float2(0.f, 0.f);
-            cre = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, cre, 0, 0, 0);
-            c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, c2, 0, 0, 0);
-            cim = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x + a.y, b.x + b.y, cim, 0, 0, 0);
-          }
-        }
-      }
-    }
-  }
-  for (int q0 = 0; q0 < nq; q0 += 2 * MMA_U) {
+  for (int m = 0; m < MT; ++m) cre[m] = cim[m] = c2[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int b0 = wv; b0 < KB; b0 += 2 * nw) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int qb = q0 + h * MMA_U;
-      if (qb >= nq) break;
-      if (qb + MMA_U < nq) load_batch(abuf[h ^ 1], qb + MMA_U);
+      const int b = b0 + h * nw;
+      if (b >= KB) break;
 #pragma unroll
-      for (int u = 0; u < MMA_U; ++u) {
-        const int kk = 4 * (ks + (qb + u) * KS) + kq;
-        const bool kok = qb + u < nq && kk < K;
-        const float2 a = (kok && arow_ok) ? abuf[h][u] : make_float2(0.f, 0.f);
-        const float2 bv = bl[min(kk, K - 1) * nrhs + colc];
-        const float2 b = (kok && col_ok) ? bv : make_float2(0.f, 0.f);
-        cre = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, cre, 0, 0, 0);
-        c2 = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, c2, 0, 0, 0);
-        cim = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x + a.y, b.x + b.y, cim, 0, 0, 0);
+      for (int u = 0; u < 4; ++u) {
+        const int k = 16 * b + (RM ? 4 * kq + u : 4 * u + kq);
+        const float2 bv = bl[k * ldb + colc];
+        const float bs = bv.x + bv.y;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const float2 av = abuf[h][m].get(u);
+          cre[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, cre[m], 0, 0, 0);
+          c2[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.y, c2[m], 0, 0, 0);
+          cim[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x + av.y, bs, cim[m], 0, 0, 0);
+        }
       }
+      if (b + 2 * nw < KB) load_block(abuf[h], b + 2 * nw);
     }
   }
-  cim = cim - cre - c2;
-  cre = cre - c2;
-  // centre inputs of this lane's output rows (for the <out, in> partial)
-  float2 ctr[4];
+  // centre inputs of the rows this thread stores (for the <out, in> partial)
+  const int mo = wv;  // wavefront m stores row tile m (MT <= nw or several each)
+  __syncthreads();
+  float2 ctr[MT][4];
 #pragma unroll
-  for (int r4 = 0; r4 < 4; ++r4) {
-    const int row = mt * 16 + 4 * kq + r4;
-    ctr[r4] = (row < n && col_ok) ? bl[row * nrhs + col] : make_float2(0.f, 0.f);
+  for (int m = 0; m < MT; ++m)
+    if (m % nw == mo) {
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) ctr[m][r4] = bl[min(16 * m + 4 * kq + r4, n - 1) * ldb + colc];
+    }
+  __syncthreads();
+  float4 *red = reinterpret_cast<float4 *>(bl);  // [nw][MT][2][64]
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const floatx4 im = cim[m] - cre[m] - c2[m], re = cre[m] - c2[m];
+    red[((wv * MT + m) * 2 + 0) * 64 + lane] = make_float4(re[0], re[1], re[2], re[3]);
+    red[((wv * MT + m) * 2 + 1) * 64 + lane] = make_float4(im[0], im[1], im[2], im[3]);
   }
-  if (KS > 1) {
-    __syncthreads();
-    float *red = reinterpret_cast<float *>(bl);
-    if (ks > 0) {
-      float *d = red + (((size_t)(ks - 1) * MT + mt) * 64 + lane) * 8;
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    if (m % nw != mo) continue;
+    float4 re = red[(m * 2 + 0) * 64 + lane], im = red[(m * 2 + 1) * 64 + lane];
+    for (int q = 1; q < nw; ++q) {
+      const float4 x = red[((q * MT + m) * 2 + 0) * 64 + lane], y = red[((q * MT + m) * 2 + 1) * 64 + lane];
+      re.x += x.x; re.y += x.y; re.z += x.z; re.w += x.w;
+      im.x += y.x; im.y += y.y; im.z += y.z; im.w += y.w;
+    }
+    const float rr[4] = {re.x, re.y, re.z, re.w}, ii[4] = {im.x, im.y, im.z, im.w};
+    double t0 = 0.0, t1 = 0.0, t2 = 0.0;
+    if (col < nrhs) {
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
-        d[r4] = cre[r4];
-        d[4 + r4] = cim[r4];
-      }
-    }
-    __syncthreads();
-    if (ks == 0) {
-      for (int q = 1; q < KS; ++q) {
-        const float *d = red + (((size_t)(q - 1) * MT + mt) * 64 + lane) * 8;
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          cre[r4] += d[r4];
-          cim[r4] += d[4 + r4];
+        const int row = 16 * m + 4 * kq + r4;
+        if (row < n) {
+          float2 o = make_float2(rr[r4], ii[r4]);
+          if (dagger && row >= half) o = make_float2(-o.x, -o.y);
+          out[((size_t)col * g.V + s) * n + row] = o;
+          const float2 c = ctr[m][r4];
+          t0 += (double)o.x * c.x + (double)o.y * c.y;
+          t1 += (double)o.x * c.y - (double)o.y * c.x;
+          t2 += (double)o.x * o.x + (double)o.y * o.y;
         }
       }
     }
-  }
-  double t0 = 0.0, t1 = 0.0, t2 = 0.0;
-  if (ks == 0) {
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const int row = mt * 16 + 4 * kq + r4;
-      if (row < n && col_ok) {
-        float2 o = make_float2(cre[r4], cim[r4]);
-        if (dagger && row >= half) o = make_float2(-o.x, -o.y);
-        out[((size_t)col * g.V + s) * n + row] = o;
-        const float2 c = ctr[r4];
-        t0 += (double)o.x * c.x + (double)o.y * c.y;
-        t1 += (double)o.x * c.y - (double)o.y * c.x;
-        t2 += (double)o.x * o.x + (double)o.y * o.y;
-      }
-    }
+    pr[m][lane][0] = t0;
+    pr[m][lane][1] = t1;
+    pr[m][lane][2] = t2;
   }
   if (part == nullptr) return;
-  if (ks == 0) {
-    pr[mt][lane][0] = t0;
-    pr[mt][lane][1] = t1;
-    pr[mt][lane][2] = t2;
-  }
   __syncthreads();
   if (tid < nrhs) {
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
@@ -906,9 +856,11 @@ __global__ __launch_bounds__(1024) void k_coarse_mma(Geom g, int n, const S *__r
   }
 }
 
+// Wavefronts per workgroup of variant ks (or 8 + ks): the K range in 2 ks shares.
+static int mma_waves(int ks) { return 2 * ks; }
 static size_t mma_lds_bytes(int n, int nrhs, int ks) {
-  const size_t b = (size_t)9 * n * nrhs * sizeof(float2);
-  const size_t r = (size_t)(ks - 1) * ((n + 15) / 16) * 64 * 8 * sizeof(float);
+  const size_t b = (size_t)((9 * n + 15) / 16 * 16) * (nrhs | 1) * sizeof(float2);
+  const size_t r = (size_t)mma_waves(ks) * ((n + 15) / 16) * 2 * 64 * sizeof(float4);
   return b > r ? b : r;
 }
 
@@ -917,8 +869,7 @@ bool coarse_mma_ok(int n, int nrhs, int variant) {
   if (n > COARSE_NMAX || nrhs < 1 || nrhs > MMA_NR) return false;
   if (variant != ks && (variant != (ks | 8) || n % 4 != 0)) return false;  // row-major copy: 16-byte rows
   if (ks != 1 && ks != 2 && ks != 4) return false;
-  if (((n + 15) / 16) * ks * 64 > 1024) return false;
-  return mma_lds_bytes(n, nrhs, ks) <= 56 * 1024;  // + 8 KB static LDS
+  return (size_t)9 * n * nrhs * sizeof(float2) <= 56 * 1024;
 }
 
 // Workgroups per coarse site.  Splitting a site's rows over several
@@ -950,20 +901,16 @@ hipError_t coarse_apply_k(const Geom &g, int n, const S *L, const c_t<R> *in, c_
       if (!coarse_mma_ok(n, nrhs, a.variant)) return hipErrorInvalidValue;
       if (rm && a.lt == nullptr) return hipErrorInvalidValue;
       const S *Lk = rm ? static_cast<const S *>(a.lt) : L;
-      const dim3 block(64 * ((n + 15) / 16) * ks);
+      const dim3 block(64 * mma_waves(ks));
       const size_t lds = mma_lds_bytes(n, nrhs, ks);
-#define MG_MMA_LAUNCH(KSV, RMV)                                                                                 \
-  hipLaunchKernelGGL((k_coarse_mma<S, KSV, RMV>), dim3(g.V), block, lds, st, g, n, Lk, in, out, nrhs, dagger, \
+#define MG_MMA_LAUNCH(MTV, RMV)                                                                                 \
+  hipLaunchKernelGGL((k_coarse_mma<S, MTV, RMV>), dim3(g.V), block, lds, st, g, n, Lk, in, out, nrhs, dagger, \
                      a.part, a.pw, a.done, c)
-      if (ks == 1) {
-        if (rm) MG_MMA_LAUNCH(1, true);
-        else MG_MMA_LAUNCH(1, false);
-      } else if (ks == 2) {
-        if (rm) MG_MMA_LAUNCH(2, true);
-        else MG_MMA_LAUNCH(2, false);
-      } else {
-        if (rm) MG_MMA_LAUNCH(4, true);
-        else MG_MMA_LAUNCH(4, false);
+      switch ((n + 15) / 16) {
+        case 1: if (rm) MG_MMA_LAUNCH(1, true); else MG_MMA_LAUNCH(1, false); break;
+        case 2: if (rm) MG_MMA_LAUNCH(2, true); else MG_MMA_LAUNCH(2, false); break;
+        case 3: if (rm) MG_MMA_LAUNCH(3, true); else MG_MMA_LAUNCH(3, false); break;
+        default: if (rm) MG_MMA_LAUNCH(4, true); else MG_MMA_LAUNCH(4, false); break;
       }
 #undef MG_MMA_LAUNCH
       return hipGetLastError();
