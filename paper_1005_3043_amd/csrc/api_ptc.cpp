@@ -1,6 +1,7 @@
 // C ABI of the learned null-vector proposal (parallel-transport network):
 // context with packed FP32 links and work buffers, forward pass, fused
 // forward + subspace-fit loss + backward pass, and the Adam step.
+#include <algorithm>
 #include <cmath>
 #include <new>
 
@@ -67,7 +68,7 @@ extern "C" int ptc_create(const mg_lattice_t *lat, const int block[4], int n_hid
   if (rc == MG_OK) rc = c->Y.alloc(F * n_out);
   if (rc == MG_OK) rc = c->Z.alloc(4);
   if (rc == MG_OK) rc = c->loss.alloc(4);
-  if (rc == MG_OK) rc = c->part.alloc(256);
+  if (rc == MG_OK) rc = c->part.alloc(PTC_NBLOCKS);
   if (rc == MG_OK) rc = c->flag.alloc(4);
   if (rc != MG_OK) {
     delete c;
@@ -122,7 +123,8 @@ extern "C" int ptc_loss_grad(ptc_ctx_t *c, const void *W1, const void *W2, const
   MG_TRY(c->lpart.alloc(2 * (size_t)g.Vc));
   MG_TRY(c->GR.alloc(2 * (size_t)g.Vc * no * (no + nt)));
   MG_TRY(c->C.alloc(2 * (size_t)g.Vc * no * nt));
-  MG_TRY(c->wpart.alloc((size_t)no * nh * PTC_HOPS * PTC_WCHUNK * 16));
+  MG_TRY(c->wpart.alloc((size_t)16 * PTC_HOPS * std::max((size_t)no * nh * ptc_wchunks(nh, no),
+                                                          (size_t)nh * ptc_wchunks(1, nh))));
   PK(pack_field<float>(g, (const double2 *)eta, c->eta, 12, 1, st));
   MG_TRY(forward_impl(c, (const float2 *)W1, (const float2 *)W2, st));
   PK(hipMemsetAsync(c->flag, 0, sizeof(int), st));

@@ -85,3 +85,32 @@ def test_errors(cuda):
     with pytest.raises(mgwd.MGError) as e:
         mgwd.PTC((8, 8, 8, 8), (4, 4, 4, 4), 8, 40)
     assert e.value.rc == -1
+
+
+@pytest.mark.parametrize("L,block,nh,no,nt", [
+    ((4, 4, 4, 4), (2, 2, 2, 2), 1, 1, 9),      # one channel, more targets than a tile's fill
+    ((6, 2, 4, 6), (3, 1, 2, 3), 2, 17, 17),    # 18-site blocks (not whole groups of four), one past a row tile
+    ((2, 2, 3, 4), (2, 1, 3, 2), 5, 7, 40),     # volume below one 64-site tile, three target tiles
+    ((8, 4, 4, 4), (4, 4, 4, 4), 8, 32, 32),    # the largest output count
+])
+def test_matrix_core_edges(cuda, L, block, nh, no, nt):
+    """Forward pass, loss and both weight gradients where rows, columns, hops
+    and sites are not whole matrix-core tiles (bounds as above)."""
+    import paper_1005_3043_amd as mgwd
+    U, eta, V = W.gauge_field(L, 0.3, 11), W.noise_spinor(L, 11), W.gaussian_spinor(L, 12, batch=(nt,))
+    W1, W2 = (w.astype(np.complex64) for w in W.ptc_init_weights(nh, no, 11))
+    net = mgwd.PTC(L, block, nh, no)
+    net.set_links(torch.from_numpy(U).cuda())
+    net.set_targets(torch.from_numpy(V).cuda())
+    d1, d2, de = torch.from_numpy(W1).cuda(), torch.from_numpy(W2).cuda(), torch.from_numpy(eta).cuda()
+    W1r, W2r = W1.astype(np.complex128), W2.astype(np.complex128)
+    _, Yref = op.forward(W1r, W2r, U, eta)
+    assert _rel(net.forward(d1, d2, de).cpu().numpy(), Yref) < 2e-6
+    loss, g1, g2 = net.loss_grad(d1, d2, de)
+    lref, g1r, g2r = op.loss_and_grad(W1r, W2r, U, eta, V, tr.BlockGeometry(L, block))
+    assert abs(loss - lref) / lref < 1e-5
+    # the fit's conditioning multiplies the FP32 rounding of Y (2e-7) once more
+    cond = max(np.linalg.cond(b) for b in
+               tr.BlockGeometry(L, block).blockify(tr.fine_to_generic(Yref)).transpose(1, 2, 3, 0).reshape(-1, int(np.prod(block)) * 6, no))
+    tol = max(1e-4, 1e-6 * cond)
+    assert _rel(g1.cpu().numpy(), g1r) < tol and _rel(g2.cpu().numpy(), g2r) < tol
