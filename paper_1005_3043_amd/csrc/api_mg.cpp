@@ -102,12 +102,12 @@ template <typename T> struct AsyncBuf {
 // canonical <-> internal for a vector of level l (FP64)
 hipError_t pack_level(mg_ctx *c, int l, const void *canon, double2 *internal, int nvec, hipStream_t st) {
   const Level &L = c->lev[l];
-  if (l == 0) return pack_field<double>(L.g, (const double2 *)canon, internal, 12, nvec, st);
+  if (l == 0) return pack_field<double>(L.g, (const double2 *)canon, internal, nvec, st);
   return pack_aos<double>(L.g, (const double2 *)canon, internal, L.n, nvec, st);
 }
 hipError_t unpack_level(mg_ctx *c, int l, const double2 *internal, void *canon, int nvec, hipStream_t st) {
   const Level &L = c->lev[l];
-  if (l == 0) return unpack_field<double>(L.g, internal, (double2 *)canon, 12, nvec, st);
+  if (l == 0) return unpack_field<double>(L.g, internal, (double2 *)canon, nvec, st);
   return unpack_aos<double>(L.g, internal, (double2 *)canon, L.n, nvec, st);
 }
 
@@ -420,7 +420,7 @@ extern "C" int mg_solve(mg_ctx_t *ctx, const void *b, void *x, int nrhs, double 
   hipStream_t s2 = c->sti;
   HIPK(hipEventRecord(c->ev_in, st));
   HIPK(hipStreamWaitEvent(s2, c->ev_in, 0));
-  HIPK(pack_field<double>(c->lev[0].g, (const double2 *)b, c->gb, 12, nrhs, s2));
+  HIPK(pack_field<double>(c->lev[0].g, (const double2 *)b, c->gb, nrhs, s2));
   int iters[MG_MAX_RHS];
   double relres[MG_MAX_RHS];
   const int rc = fgcr(c, c->gb, c->gx, nrhs, tol, iters, relres, s2);
@@ -428,7 +428,7 @@ extern "C" int mg_solve(mg_ctx_t *ctx, const void *b, void *x, int nrhs, double 
     (void)hipStreamSynchronize(s2);
     return rc;
   }
-  HIPK(unpack_field<double>(c->lev[0].g, c->gx, (double2 *)x, 12, nrhs, s2));
+  HIPK(unpack_field<double>(c->lev[0].g, c->gx, (double2 *)x, nrhs, s2));
   HIPK(hipEventRecord(c->ev_out, s2));
   HIPK(hipStreamWaitEvent(st, c->ev_out, 0));
   HIPK(hipStreamSynchronize(s2));
@@ -483,13 +483,13 @@ extern "C" int mg_vcycle(mg_ctx_t *ctx, mg_prec_t prec, const void *in, void *ou
   hipStream_t s2 = c->sti;
   HIPK(hipEventRecord(c->ev_in, st));
   HIPK(hipStreamWaitEvent(s2, c->ev_in, 0));
-  HIPK(pack_field<double>(L0.g, (const double2 *)in, a, 12, nrhs, s2));
+  HIPK(pack_field<double>(L0.g, (const double2 *)in, a, nrhs, s2));
   const int rc = precondition_at(c, prec, a, b, nrhs, s2);
   if (rc < 0) {
     (void)hipStreamSynchronize(s2);
     return rc;
   }
-  HIPK(unpack_field<double>(L0.g, b, (double2 *)out, 12, nrhs, s2));
+  HIPK(unpack_field<double>(L0.g, b, (double2 *)out, nrhs, s2));
   HIPK(hipStreamSynchronize(s2));
   if (cgnr_iters) *cgnr_iters = (int)c->n_cgnr;
   return MG_OK;

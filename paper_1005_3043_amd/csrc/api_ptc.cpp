@@ -93,7 +93,7 @@ extern "C" int ptc_set_targets(ptc_ctx_t *c, const void *V, int nv, hipStream_t 
   const size_t F = (size_t)12 * c->g.Vpad;
   MG_TRY(c->V.alloc(F * nv));
   c->nt = nv;
-  PK(pack_field<float>(c->g, (const double2 *)V, c->V, 12, nv, st));
+  PK(pack_field<float>(c->g, (const double2 *)V, c->V, nv, st));
   PK(ptc_norm2(c->V, F * nv, c->part, c->Z, st));
   return MG_OK;
 }
@@ -101,9 +101,9 @@ extern "C" int ptc_set_targets(ptc_ctx_t *c, const void *V, int nv, hipStream_t 
 extern "C" int ptc_forward(ptc_ctx_t *c, const void *W1, const void *W2, const void *eta, void *Y, hipStream_t st) {
   set_error("");
   if (!c || !W1 || !W2 || !eta || !Y) return (set_error("ptc_forward: NULL argument"), MG_EINVAL);
-  PK(pack_field<float>(c->g, (const double2 *)eta, c->eta, 12, 1, st));
+  PK(pack_field<float>(c->g, (const double2 *)eta, c->eta, 1, st));
   MG_TRY(forward_impl(c, (const float2 *)W1, (const float2 *)W2, st));
-  PK(unpack_field<float>(c->g, c->Y, (double2 *)Y, 12, c->nout, st));
+  PK(unpack_field<float>(c->g, c->Y, (double2 *)Y, c->nout, st));
   return MG_OK;
 }
 
@@ -125,7 +125,7 @@ extern "C" int ptc_loss_grad(ptc_ctx_t *c, const void *W1, const void *W2, const
   MG_TRY(c->C.alloc(2 * (size_t)g.Vc * no * nt));
   MG_TRY(c->wpart.alloc((size_t)16 * PTC_HOPS * std::max((size_t)no * nh * ptc_wchunks(nh, no),
                                                           (size_t)nh * ptc_wchunks(1, nh))));
-  PK(pack_field<float>(g, (const double2 *)eta, c->eta, 12, 1, st));
+  PK(pack_field<float>(g, (const double2 *)eta, c->eta, 1, st));
   MG_TRY(forward_impl(c, (const float2 *)W1, (const float2 *)W2, st));
   PK(hipMemsetAsync(c->flag, 0, sizeof(int), st));
   PK(ptc_fit(g, no, nt, c->Y, c->V, c->Z, c->GR, c->C, c->flag, c->gY, c->lpart, c->loss, st));

@@ -6,14 +6,12 @@
 
 namespace mg {
 
-// ---- pack.hip: canonical complex128 [nvec][sites lex][ncomp] <-> internal
-//      tile-interleaved fine fields (fidx), nvec fields of ncomp * Vpad entries.
+// ---- pack.hip: canonical complex128 [nvec][sites lex][12] <-> internal
+//      tile-interleaved fine fields (fidx), nvec fields of 12 * Vpad entries.
 template <typename T>
-hipError_t pack_field(const Geom &g, const double2 *canon, c_t<T> *internal, int ncomp, int nvec,
-                      hipStream_t st);
+hipError_t pack_field(const Geom &g, const double2 *canon, c_t<T> *internal, int nvec, hipStream_t st);
 template <typename T>
-hipError_t unpack_field(const Geom &g, const c_t<T> *internal, double2 *canon, int ncomp, int nvec,
-                        hipStream_t st);
+hipError_t unpack_field(const Geom &g, const c_t<T> *internal, double2 *canon, int nvec, hipStream_t st);
 // canonical gauge field U[4][lex site][3][3] -> internal 36-component field
 template <typename T> hipError_t pack_gauge(const Geom &g, const double2 *canon, c_t<T> *internal, hipStream_t st);
 

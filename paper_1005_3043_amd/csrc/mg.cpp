@@ -1757,7 +1757,7 @@ int setup(mg_ctx *c, const void *U, hipStream_t st) {
     const size_t nvs = Lv.vsize() * Lv.nv;
     MG_TRY(Lv.NV.alloc(nvs));
     MG_TRY(Lv.P64.alloc(nvs));
-    if (l == 0) HIPK(pack_field<double>(Lv.g, (const double2 *)p.init_vectors[0], Lv.NV, 12, Lv.nv, st));
+    if (l == 0) HIPK(pack_field<double>(Lv.g, (const double2 *)p.init_vectors[0], Lv.NV, Lv.nv, st));
     else HIPK(pack_aos<double>(Lv.g, (const double2 *)p.init_vectors[l], Lv.NV, Lv.n, Lv.nv, st));
     MG_TRY(relax(c, l, Lv.NV, Lv.nv, st));
     MG_TRY(refine(c, l, st));
