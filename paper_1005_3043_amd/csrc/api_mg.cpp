@@ -266,19 +266,47 @@ extern "C" int mg_transfer_variant(mg_ctx_t *ctx, mg_prec_t prec, int nrhs, int 
   return MG_OK;
 }
 
+namespace {
+// FP64 transfers between canonical arrays.  The finest level's go straight
+// to and from the caller's fine vectors; the coarse ones, which are small,
+// are converted.
+int restrict_f64(mg_ctx *c, int level, const void *fine, void *coarse, int nrhs, hipStream_t st) {
+  Level &L = c->lev[level], &Lc = c->lev[level + 1];
+  AsyncBuf<double2> a(st), b(st);
+  HIPK(b.alloc(Lc.vsize() * nrhs));
+  if (level == 0) {
+    HIPK(restrict_fine_f64<true>(L.g, Lc.g, L.nv, L.P64, (const double2 *)fine, b.p, nrhs, st));
+  } else {
+    HIPK(a.alloc(L.vsize() * nrhs));
+    HIPK(pack_level(c, level, fine, a.p, nrhs, st));
+    MG_TRY(transfer_restrict<PF64>(c, level, a.p, b.p, nrhs, st));
+  }
+  HIPK(unpack_level(c, level + 1, b.p, coarse, nrhs, st));
+  return MG_OK;
+}
+int prolong_f64(mg_ctx *c, int level, const void *coarse, void *fine, int nrhs, hipStream_t st) {
+  Level &L = c->lev[level], &Lc = c->lev[level + 1];
+  AsyncBuf<double2> a(st), b(st);
+  HIPK(b.alloc(Lc.vsize() * nrhs));
+  HIPK(pack_level(c, level + 1, coarse, b.p, nrhs, st));
+  if (level == 0) {
+    HIPK(prolong_fine_f64<true>(L.g, Lc.g, L.nv, L.P64, b.p, (double2 *)fine, nrhs, 0, st));
+  } else {
+    HIPK(a.alloc(L.vsize() * nrhs));
+    MG_TRY(transfer_prolong<PF64>(c, level, b.p, a.p, nrhs, 0, st));
+    HIPK(unpack_level(c, level, a.p, fine, nrhs, st));
+  }
+  return MG_OK;
+}
+}  // namespace
+
 extern "C" int mg_restrict(mg_ctx_t *ctx, int level, const void *fine, void *coarse, int nrhs, hipStream_t st) {
   set_error("");
   if (!ctx) return bad(MG_EINVAL, "ctx is NULL");
   MG_TRY(check_ctx_level(ctx, level, 0, ctx->nlev - 2));
   if (!fine || !coarse || nrhs < 1) return bad(MG_EINVAL, "mg_restrict: bad buffers or nrhs");
   MG_TRY(ensure_scalars(ctx, part_need(ctx, 1)));
-  AsyncBuf<double2> a(st), b(st);
-  HIPK(a.alloc(ctx->lev[level].vsize() * nrhs));
-  HIPK(b.alloc(ctx->lev[level + 1].vsize() * nrhs));
-  HIPK(pack_level(ctx, level, fine, a.p, nrhs, st));
-  MG_TRY(transfer_restrict<PF64>(ctx, level, a.p, b.p, nrhs, st));
-  HIPK(unpack_level(ctx, level + 1, b.p, coarse, nrhs, st));
-  return MG_OK;
+  return restrict_f64(ctx, level, fine, coarse, nrhs, st);
 }
 
 extern "C" int mg_prolong(mg_ctx_t *ctx, int level, const void *coarse, void *fine, int nrhs, hipStream_t st) {
@@ -286,13 +314,7 @@ extern "C" int mg_prolong(mg_ctx_t *ctx, int level, const void *coarse, void *fi
   if (!ctx) return bad(MG_EINVAL, "ctx is NULL");
   MG_TRY(check_ctx_level(ctx, level, 0, ctx->nlev - 2));
   if (!fine || !coarse || nrhs < 1) return bad(MG_EINVAL, "mg_prolong: bad buffers or nrhs");
-  AsyncBuf<double2> a(st), b(st);
-  HIPK(a.alloc(ctx->lev[level].vsize() * nrhs));
-  HIPK(b.alloc(ctx->lev[level + 1].vsize() * nrhs));
-  HIPK(pack_level(ctx, level + 1, coarse, b.p, nrhs, st));
-  MG_TRY(transfer_prolong<PF64>(ctx, level, b.p, a.p, nrhs, 0, st));
-  HIPK(unpack_level(ctx, level, a.p, fine, nrhs, st));
-  return MG_OK;
+  return prolong_f64(ctx, level, coarse, fine, nrhs, st);
 }
 
 extern "C" int coarse_apply(mg_ctx_t *ctx, int level, const void *in, void *out, int nrhs, int dagger,
@@ -330,24 +352,19 @@ template <typename P> int apply_op_t(mg_ctx *c, int level, const double2 *a, dou
 }  // namespace
 
 namespace {
+// FP32 arithmetic (P = PF32 or PF16) on FP64 vectors in the internal layout
 template <typename P>
 int transfer_t(mg_ctx *c, int level, int dir, const double2 *a, double2 *b, int nrhs, hipStream_t st) {
-  using R = typename P::R;
-  if constexpr (sizeof(R) == 8) {
-    if (dir == 0) return transfer_restrict<P>(c, level, a, b, nrhs, st);
-    return transfer_prolong<P>(c, level, a, b, nrhs, 0, st);
-  } else {
-    const size_t nf = c->lev[level].vsize() * nrhs, nc = c->lev[level + 1].vsize() * nrhs;
-    const size_t nin = dir == 0 ? nf : nc, nout = dir == 0 ? nc : nf;
-    AsyncBuf<float2> x(st), y(st);
-    HIPK(x.alloc(nin));
-    HIPK(y.alloc(nout));
-    HIPK((convert<float, double>(x.p, a, nin, st)));
-    if (dir == 0) MG_TRY(transfer_restrict<P>(c, level, x.p, y.p, nrhs, st));
-    else MG_TRY(transfer_prolong<P>(c, level, x.p, y.p, nrhs, 0, st));
-    HIPK((convert<double, float>(b, y.p, nout, st)));
-    return MG_OK;
-  }
+  const size_t nf = c->lev[level].vsize() * nrhs, nc = c->lev[level + 1].vsize() * nrhs;
+  const size_t nin = dir == 0 ? nf : nc, nout = dir == 0 ? nc : nf;
+  AsyncBuf<float2> x(st), y(st);
+  HIPK(x.alloc(nin));
+  HIPK(y.alloc(nout));
+  HIPK((convert<float, double>(x.p, a, nin, st)));
+  if (dir == 0) MG_TRY(transfer_restrict<P>(c, level, x.p, y.p, nrhs, st));
+  else MG_TRY(transfer_prolong<P>(c, level, x.p, y.p, nrhs, 0, st));
+  HIPK((convert<double, float>(b, y.p, nout, st)));
+  return MG_OK;
 }
 }  // namespace
 
@@ -362,14 +379,15 @@ extern "C" int mg_transfer(mg_ctx_t *ctx, int level, mg_prec_t prec, int directi
     return bad(MG_ENOTSUP, "mg_transfer: prec must be MG_F64, MG_F32 or MG_F16");
   MG_TRY(ensure_prec(ctx, prec, st));
   MG_TRY(ensure_scalars(ctx, part_need(ctx, 1)));
+  if (prec == MG_F64)
+    return direction == 0 ? restrict_f64(ctx, level, in, out, nrhs, st) : prolong_f64(ctx, level, in, out, nrhs, st);
   const int lin = direction == 0 ? level : level + 1, lout = direction == 0 ? level + 1 : level;
   AsyncBuf<double2> a(st), b(st);
   HIPK(a.alloc(ctx->lev[lin].vsize() * nrhs));
   HIPK(b.alloc(ctx->lev[lout].vsize() * nrhs));
   HIPK(pack_level(ctx, lin, in, a.p, nrhs, st));
   int rc;
-  if (prec == MG_F64) rc = transfer_t<PF64>(ctx, level, direction, a.p, b.p, nrhs, st);
-  else if (prec == MG_F32) rc = transfer_t<PF32>(ctx, level, direction, a.p, b.p, nrhs, st);
+  if (prec == MG_F32) rc = transfer_t<PF32>(ctx, level, direction, a.p, b.p, nrhs, st);
   else rc = transfer_t<PF16>(ctx, level, direction, a.p, b.p, nrhs, st);
   MG_TRY(rc);
   HIPK(unpack_level(ctx, lout, b.p, out, nrhs, st));

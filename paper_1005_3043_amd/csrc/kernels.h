@@ -197,6 +197,15 @@ hipError_t restrict_fine(const Geom &g, const Geom &gc, int nv, const S *P, cons
 template <typename R, typename S>
 hipError_t prolong_fine(const Geom &g, const Geom &gc, int nv, const S *P, const c_t<R> *coarse, c_t<R> *fine,
                         int nrhs, int accumulate, hipStream_t st);
+// FP64 on the matrix cores (transfer_f64.hip): fine vectors in the fine
+// layout, or canonical arrays (CANON, [nrhs][site][12] lexicographic).
+// Aggregates of at most 256 sites, nv <= 32, any nrhs.
+template <bool CANON>
+hipError_t restrict_fine_f64(const Geom &g, const Geom &gc, int nv, const double2 *P, const double2 *fine,
+                             double2 *coarse, int nrhs, hipStream_t st);
+template <bool CANON>
+hipError_t prolong_fine_f64(const Geom &g, const Geom &gc, int nv, const double2 *P, const double2 *coarse,
+                            double2 *fine, int nrhs, int accumulate, hipStream_t st);
 // Many right-hand sides on the FP32 matrix cores (transfer_mma.hip):
 // one workgroup per aggregate for all nrhs <= 16; requires |B| % 4 == 0.
 bool transfer_mma_ok(const Geom &g, int nv, int nrhs);
