@@ -648,6 +648,31 @@ template <> struct Op4<float2> {
 
 constexpr int MMA_NR = 16;  // right-hand sides per GEMM tile (N of the MFMA)
 
+// The convergence prologue for all right-hand sides of a workgroup (rsum:
+// LDS); true when every one has converged.  ||r||^2 of right-hand side r by
+// wavefront r mod nw, then lane r of every wavefront tests right-hand side r
+// (one after another, their loads alone took a round trip each).
+__device__ __forceinline__ bool cg_check_all(const CgCheck &chk, int nrhs, double *rsum) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  for (int r = wv; r < nrhs; r += nw) {
+    double t = 0.0;
+    for (int i = lane; i < chk.np_r; i += 64) t += chk.part_r[(size_t)r * chk.np_r + i];
+    t = wave_sum(t);
+    if (lane == 0) rsum[r] = t;
+  }
+  const int r = min(lane, nrhs - 1);
+  const double *cg = chk.cg + (size_t)r * CG_NS;
+  const double lim = cg[4] * cg[3];
+  const int was = chk.done[r], iter = chk.it_in[r];
+  __syncthreads();
+  const bool conv = was != 0 || !(rsum[r] > lim) || iter + 1 >= chk.maxit;
+  if (blockIdx.x == 0 && wv == 0 && lane < nrhs && was == 0) {
+    chk.it_out[r] = iter + 1;
+    if (conv) chk.done[r] = 1;
+  }
+  return __all(conv);
+}
+
 // One workgroup per coarse site.  Every wavefront accumulates all MT =
 // ceil(n / 16) row tiles of all right-hand sides over its share of the K
 // range: blocks of 16 of the 9n (slot, column) pairs, block b to wavefront b
@@ -678,28 +703,7 @@ __global__ __launch_bounds__(512) void k_coarse_mma(Geom g, int n, const S *__re
     const int d = lane < nrhs ? done[lane] : 1;
     if (__all(d != 0)) return;
   }
-  if (chk.part_r != nullptr) {
-    // ||r||^2 of right-hand side r by wavefront r mod nw, then lane r of every
-    // wavefront tests right-hand side r (one after another, their loads alone
-    // took a round trip each)
-    for (int r = wv; r < nrhs; r += nw) {
-      double t = 0.0;
-      for (int i = lane; i < chk.np_r; i += 64) t += chk.part_r[(size_t)r * chk.np_r + i];
-      t = wave_sum(t);
-      if (lane == 0) rsum[r] = t;
-    }
-    const int r = min(lane, nrhs - 1);
-    const double *cg = chk.cg + (size_t)r * CG_NS;
-    const double lim = cg[4] * cg[3];
-    const int was = chk.done[r], iter = chk.it_in[r];
-    __syncthreads();
-    const bool conv = was != 0 || !(rsum[r] > lim) || iter + 1 >= chk.maxit;
-    if (blockIdx.x == 0 && wv == 0 && lane < nrhs && was == 0) {
-      chk.it_out[r] = iter + 1;
-      if (conv) chk.done[r] = 1;
-    }
-    if (__all(conv)) return;
-  }
+  if (chk.part_r != nullptr && cg_check_all(chk, nrhs, rsum)) return;
   const uint32_t s = xcd_remap(blockIdx.x, gridDim.x);
   const int K = 9 * n, half = n >> 1, KB = (K + 15) >> 4, ldb = nrhs | 1;
   const int kq = lane >> 4, col = lane & 15;
@@ -856,6 +860,165 @@ __global__ __launch_bounds__(512) void k_coarse_mma(Geom g, int n, const S *__re
   }
 }
 
+// FP64: the same product on the FP64 matrix cores (16x16x4; C lane l, register
+// v = row 4 v + l / 16).  One workgroup of three wavefronts per coarse site and
+// group of right-hand sides; wavefront w takes stencil slots w, w + 3, w + 6,
+// stages a slot's vectors in its own LDS and reads its operator block once, so
+// no barrier stands between the slots.  Bound by the operator's bytes: with
+// one workgroup per right-hand side (k_coarse) 12 of them on 24^3 x 48 (n =
+// 48, 860 MB) took 638 us.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int MF_WAVES = 3;
+
+template <int MT>
+__global__ __launch_bounds__(64 * MF_WAVES) void k_coarse_mma_f64(Geom g, int n, const double2 *__restrict__ L,
+                                                                  const double2 *__restrict__ in,
+                                                                  double2 *__restrict__ out, int nrhs, int per,
+                                                                  int dagger, double *__restrict__ part, int pw,
+                                                                  const int *__restrict__ done, CgCheck chk) {
+  extern __shared__ __align__(16) double2 bl64[];  // [MF_WAVES][4 KS][ldb], then the wavefronts' sums
+  __shared__ double rsum[MMA_NR];
+  __shared__ double pr[MT][64][3];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = blockIdx.y * per, nr = min(per, nrhs - r0);
+  if (done != nullptr) {
+    const int d = lane < nr ? done[r0 + lane] : 1;
+    if (__all(d != 0)) return;
+  }
+  if (chk.part_r != nullptr && cg_check_all(chk, nrhs, rsum)) return;
+  const uint32_t s = xcd_remap(blockIdx.x, gridDim.x);
+  const int half = n >> 1, KS = (n + 3) >> 2, ldb = nr | 1;
+  const int q = lane >> 4, col = lane & 15, colc = col < nr ? col : 0;
+  double2 *bw = bl64 + (size_t)wv * 4 * KS * ldb;
+  int row[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) row[m] = min(16 * m + col, n - 1);
+  const uint32_t nb = slot_site(g, s, lane < 9 ? lane : 0);
+  const int j = min(lane, n - 1);
+  const bool neg = dagger && j >= half;
+  doublex4 re[MT], im[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) re[m] = im[m] = doublex4{0.0, 0.0, 0.0, 0.0};
+  constexpr int U = 4;  // k-steps per load batch
+  double2 a[U][MT];
+  for (int slot = wv; slot < 9; slot += MF_WAVES) {
+    const double2 *Ls = L + ((size_t)s * 9 + slot) * n * n;
+    auto load = [&](int k0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const size_t o = (size_t)min(4 * (k0 + u) + q, n - 1) * n;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) a[u][m] = Ls[o + row[m]];
+      }
+    };
+    load(0);
+    {
+      const double2 *src = in + ((size_t)r0 * g.V + __builtin_amdgcn_readlane(nb, slot)) * n + j;
+      const size_t vs = (size_t)g.V * n;
+      __builtin_amdgcn_wave_barrier();
+      for (int t0 = 0; t0 < nr; t0 += 4) {
+        double2 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src[(size_t)min(t0 + u, nr - 1) * vs];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          bw[j * ldb + min(t0 + u, nr - 1)] = neg ? make_double2(-v[u].x, -v[u].y) : v[u];
+      }
+      for (int i = n * ldb + lane; i < 4 * KS * ldb; i += 64) bw[i] = make_double2(0.0, 0.0);
+      __builtin_amdgcn_wave_barrier();
+    }
+    for (int k0 = 0; k0 < KS; k0 += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (k0 + u >= KS) break;
+        const double2 b = bw[(4 * (k0 + u) + q) * ldb + colc];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const double2 p = a[u][m];
+          re[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.x, re[m], 0, 0, 0);
+          im[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.y, im[m], 0, 0, 0);
+          re[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(-p.y, b.y, re[m], 0, 0, 0);
+          im[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, b.x, im[m], 0, 0, 0);
+        }
+        if (k0 + U + u < KS) {  // the k-step after next U takes this one's registers
+          const size_t o = (size_t)min(4 * (k0 + U + u) + q, n - 1) * n;
+#pragma unroll
+          for (int m = 0; m < MT; ++m) a[u][m] = Ls[o + row[m]];
+        }
+      }
+    }
+  }
+  // sums of wavefronts 1 and 2 to wavefront 0; slot 0, the centre, was wavefront 0's first
+  __syncthreads();
+  if (wv > 0) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) bl64[(((wv - 1) * MT + m) * 4 + v) * 64 + lane] = make_double2(re[m][v], im[m][v]);
+  }
+  __syncthreads();
+  if (wv == 0) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      double t0 = 0.0, t1 = 0.0, t2 = 0.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double2 o = make_double2(re[m][v], im[m][v]);
+        for (int w = 0; w < MF_WAVES - 1; ++w) o = cadd(o, bl64[((w * MT + m) * 4 + v) * 64 + lane]);
+        const int i = 16 * m + 4 * v + q;
+        if (i < n && col < nr) {
+          if (dagger && i >= half) o = make_double2(-o.x, -o.y);
+          const size_t at = ((size_t)(r0 + col) * g.V + s) * n + i;
+          out[at] = o;
+          if (part != nullptr) {
+            double2 c = make_double2(0.0, 0.0);
+            if (pw == 3) c = in[at];  // (not taken under dagger)
+            t0 += o.x * c.x + o.y * c.y;
+            t1 += o.x * c.y - o.y * c.x;
+            t2 += o.x * o.x + o.y * o.y;
+          }
+        }
+      }
+      pr[m][lane][0] = t0;
+      pr[m][lane][1] = t1;
+      pr[m][lane][2] = t2;
+    }
+  }
+  if (part == nullptr) return;
+  __syncthreads();
+  if (tid < nr) {
+    double t[3] = {0.0, 0.0, 0.0};
+    for (int m = 0; m < MT; ++m)
+      for (int g4 = 0; g4 < 4; ++g4)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t[c] += pr[m][g4 * 16 + tid][c];
+    double *p = part + ((size_t)(r0 + tid) * gridDim.x + blockIdx.x) * pw;
+    if (pw == 1) {
+      p[0] = t[2];
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) p[c] = t[c];
+    }
+  }
+}
+
+static hipError_t coarse_mma_f64(const Geom &g, int n, const double2 *L, const double2 *in, double2 *out, int nrhs,
+                                 int dagger, const CoarseArgs &a, const CgCheck &c, hipStream_t st) {
+  const int ng = (nrhs + MMA_NR - 1) / MMA_NR, per = (nrhs + ng - 1) / ng, mt = (n + 15) / 16;
+  size_t lds = sizeof(double2) * MF_WAVES * ((n + 3) / 4 * 4) * (per | 1);
+  const size_t sums = sizeof(double2) * (MF_WAVES - 1) * mt * 4 * 64;
+  if (lds < sums) lds = sums;
+#define MG_MF(M)                                                                                                    \
+  hipLaunchKernelGGL(k_coarse_mma_f64<M>, dim3(g.V, ng), dim3(64 * MF_WAVES), lds, st, g, n, L, in, out, nrhs, per, \
+                     dagger, a.part, a.pw, a.done, c)
+  if (mt == 1) MG_MF(1);
+  else if (mt == 2) MG_MF(2);
+  else if (mt == 3) MG_MF(3);
+  else MG_MF(4);
+#undef MG_MF
+  return hipGetLastError();
+}
+
 // Wavefronts per workgroup of variant ks (or 8 + ks): the K range in 2 ks shares.
 static int mma_waves(int ks) { return 2 * ks; }
 static size_t mma_lds_bytes(int n, int nrhs, int ks) {
@@ -917,6 +1080,9 @@ hipError_t coarse_apply_k(const Geom &g, int n, const S *L, const c_t<R> *in, c_
     }
   } else {
     if (a.variant > 0) return hipErrorInvalidValue;
+    // from two right-hand sides on, unless the CGNR updates are fused in
+    if (nrhs >= 2 && !(a.fuse && a.fuse->kind) && (c.part_r == nullptr || nrhs <= MMA_NR))
+      return coarse_mma_f64(g, n, L, in, out, nrhs, dagger, a, c, st);
   }
   const dim3 grid(g.V * coarse_split(n, g.V) * nrhs);
   dim3 block(coarse_threads(n, g.V));
