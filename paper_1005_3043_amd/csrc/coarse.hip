@@ -866,12 +866,14 @@ __global__ __launch_bounds__(512) void k_coarse_mma(Geom g, int n, const S *__re
 // stages a slot's vectors in its own LDS and reads its operator block once, so
 // no barrier stands between the slots.  Bound by the operator's bytes: with
 // one workgroup per right-hand side (k_coarse) 12 of them on 24^3 x 48 (n =
-// 48, 860 MB) took 638 us.
+// 48, 860 MB) took 626 us; this takes 189, 4.8 TB/s of operator and vectors.
+// Three wavefronts per SIMD: with two, whole workgroups of three leave a
+// quarter of the slots empty (228 us).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int MF_WAVES = 3;
 
 template <int MT>
-__global__ __launch_bounds__(64 * MF_WAVES) void k_coarse_mma_f64(Geom g, int n, const double2 *__restrict__ L,
+__global__ __launch_bounds__(64 * MF_WAVES, 3) void k_coarse_mma_f64(Geom g, int n, const double2 *__restrict__ L,
                                                                   const double2 *__restrict__ in,
                                                                   double2 *__restrict__ out, int nrhs, int per,
                                                                   int dagger, double *__restrict__ part, int pw,
@@ -1080,8 +1082,12 @@ hipError_t coarse_apply_k(const Geom &g, int n, const S *L, const c_t<R> *in, c_
     }
   } else {
     if (a.variant > 0) return hipErrorInvalidValue;
-    // from two right-hand sides on, unless the CGNR updates are fused in
-    if (nrhs >= 2 && !(a.fuse && a.fuse->kind) && (c.part_r == nullptr || nrhs <= MMA_NR))
+    // From two right-hand sides on (four below 1 024 sites, where a workgroup
+    // per site leaves most of the device idle), unless the CGNR updates are
+    // fused in.  2 / 4 / 12 right-hand sides, this way against one workgroup
+    // per right-hand side: n = 48, 2 592 sites 173 / 176 / 189 and 171 / 266 /
+    // 626 us; n = 40, 512 sites 31 / 31 / 34 and 22 / 32 / 84 us.
+    if (nrhs >= (g.V < 1024u ? 4 : 2) && !(a.fuse && a.fuse->kind) && (c.part_r == nullptr || nrhs <= MMA_NR))
       return coarse_mma_f64(g, n, L, in, out, nrhs, dagger, a, c, st);
   }
   const dim3 grid(g.V * coarse_split(n, g.V) * nrhs);
