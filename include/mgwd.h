@@ -161,8 +161,9 @@ typedef struct {
   int n_coarse_dispatch;        /* coarse stencil applications dispatched,
                                    including those that returned at once
                                    because their RHS had converged (those
-                                   inside a whole-solve CGNR launch are
-                                   applications, not dispatches)          */
+                                   inside a whole-solve CGNR launch of the
+                                   FP32 classes are applications, not
+                                   dispatches)                            */
   int n_cgnr_iters;             /* coarsest CGNR iterations, summed          */
   int n_vcycles;                /* preconditioner applications               */
   double t_setup_s, t_solve_s;  /* wall time of the last setup / solve       */
@@ -338,15 +339,15 @@ int mg_coarse_variant(mg_ctx_t *ctx, int level, mg_prec_t prec, int nrhs,
                       int *variant, double *us);
 
 /* Coarsest-level CGNR of a single right-hand side (paper, "Numerical
- * Results": CG on the normal equations to 10^-3 on the coarsest grid) in
- * the FP32 and FP16-storage preconditioners: on (default), all iterations
- * run in one cooperative launch that keeps each coarse site's operator rows
- * in registers and joins its two stencil phases per iteration with grid
- * barriers; off, they run as chunks of captured per-iteration launches.
+ * Results": CG on the normal equations to 10^-3 on the coarsest grid), in
+ * every precision class: on (default), all iterations run in one cooperative
+ * launch that keeps each coarse site's operator rows in registers and joins
+ * its two stencil phases per iteration with grid-wide exchanges; off, they
+ * run as chunks of captured per-iteration launches.
  * Both forms do the same arithmetic in the same order (same iterates, same
  * iteration counts).  Where the device cannot hold the whole coarse grid at
  * once (or the operator rows do not fit), the chunks run regardless.  A
- * barrier wait gives up after 2^20 polls (on >= 2: after `on` polls, to
+ * wait gives up after 2^20 polls (on >= 2: after `on` polls, to
  * exercise this path); the launch then leaves, and that coarsest solve is
  * done again from its right-hand side by the chunks, which that (level,
  * precision) keeps using until this function is called again.
@@ -370,8 +371,8 @@ int mg_set_gcr_fusion(mg_ctx_t *ctx, int mode);
  * coarse_tol ||b||, at most coarse_maxiter iterations, D_c^dag = sigma_3 D_c
  * sigma_3) with the stored coarsest operator of precision prec (MG_F64,
  * MG_F32, MG_F16 as mg_apply_op), exactly as the V-cycle runs it: one
- * whole-solve launch for one right-hand side in FP32 arithmetic (see
- * mg_set_cgnr_persistent), chunks of captured iterations otherwise.
+ * whole-solve launch for one right-hand side (see mg_set_cgnr_persistent),
+ * chunks of captured iterations otherwise.
  * b, x: DEVICE complex128 canonical vectors of the coarsest level
  * [nrhs][Lct][Lcz][Lcy][Lcx][n], not aliased; 1 <= nrhs <= 16.  iters (HOST,
  * may be NULL) receives the CGNR iterations of each right-hand side (nrhs

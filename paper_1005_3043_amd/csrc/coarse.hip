@@ -322,126 +322,223 @@ __global__ __launch_bounds__(512) void k_coarse(Geom g, int n, const S *__restri
 // The whole coarsest-level CGNR of one right-hand side in one cooperative
 // launch: the fused two-phase iteration of k_coarse (phase 1: p = z + beta
 // p_old staged, w = A p; phase 2: r = r_old - alpha w staged, e += alpha p,
-// z = A^dag r) with a grid-wide barrier after each phase instead of a kernel
-// boundary.  Each workgroup (one coarse site) loads its operator rows once
-// into registers and keeps them for every iteration; a kernel boundary would
-// drop the L2 and fetch the operator again.  Every workgroup computes the
-// same scalars from the same partials in the same order, so all of them take
-// the same exit.  A barrier wait is bounded: a workgroup that gives up sets
-// *fail and leaves, so the grid always drains.
+// z = A^dag r) with a grid-wide exchange after each phase instead of a kernel
+// boundary, its start (r = b, z = A^dag b, ||b||^2) included.  Each workgroup
+// (one coarse site) loads its operator rows once into registers and keeps
+// them for every iteration; a kernel boundary would drop the L2 and fetch the
+// operator again.  It also keeps p and r of its site and the eight neighbours
+// and repeats their updates, so that only w and z travel, and e of its site.
+// Every workgroup computes the same scalars from the same partials in the same
+// order, so all of them take the same exit.  A wait is bounded: a workgroup
+// that gives up sets *fail and leaves, so the grid always drains.
+//
+// Bound by the latency of an exchange (store, acknowledge, announce, poll,
+// load).  16^3 x 32, n = 40, FP16 storage, 512 sites, 45 iterations: 835 us a
+// launch with p and r exchanged as well and the sums acknowledged after the
+// vectors, 570 us (6.3 us per phase) now.  8^4, n = 16, FP64, 16 sites: a
+// solve of 47.2 ms as chunks of launches takes 24.2 ms.
 constexpr int CGP_PMAX = 16;          // most operator entries per thread kept in registers
 
-// Data exchanged between workgroups inside the launch (vectors and partial
-// sums) is read and written as agent-scope relaxed atomics: the loads skip
-// the XCD's non-coherent L2 and the stores write through it, so a barrier
-// needs only each thread's stores acknowledged before its arrival, and no
-// L2 write-back or invalidation (which cost about 80 us per barrier here).
-__device__ __forceinline__ float2 cld(const float2 *p) {
-  const unsigned long long v = __hip_atomic_load(reinterpret_cast<unsigned long long *>(const_cast<float2 *>(p)),
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  float2 r;
-  __builtin_memcpy(&r, &v, sizeof(r));
-  return r;
+// Data exchanged between workgroups inside the launch is read and written as
+// agent-scope relaxed atomics: the loads skip the XCD's non-coherent L2 and
+// the stores write through it, so an exchange needs only each thread's stores
+// acknowledged before its announcement, and no L2 write-back or invalidation
+// (which cost about 80 us per barrier here).
+__device__ __forceinline__ unsigned long long xld(const void *p) {
+  return __hip_atomic_load(reinterpret_cast<unsigned long long *>(const_cast<void *>(p)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void cst(float2 *p, float2 v) {
-  unsigned long long u;
-  __builtin_memcpy(&u, &v, sizeof(u));
-  __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void xst(void *p, unsigned long long v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ double cldd(const double *p) {
-  const unsigned long long v = __hip_atomic_load(reinterpret_cast<unsigned long long *>(const_cast<double *>(p)),
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  double r;
-  __builtin_memcpy(&r, &v, sizeof(r));
-  return r;
+__device__ __forceinline__ float2 cld(const float2 *p) { return __builtin_bit_cast(float2, xld(p)); }
+__device__ __forceinline__ void cst(float2 *p, float2 v) { xst(p, __builtin_bit_cast(unsigned long long, v)); }
+__device__ __forceinline__ double2 cld(const double2 *p) {
+  return make_double2(__builtin_bit_cast(double, xld(&p->x)), __builtin_bit_cast(double, xld(&p->y)));
 }
-__device__ __forceinline__ void cstd(double *p, double v) {
-  unsigned long long u;
-  __builtin_memcpy(&u, &v, sizeof(u));
-  __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void cst(double2 *p, double2 v) {
+  xst(&p->x, __builtin_bit_cast(unsigned long long, v.x));
+  xst(&p->y, __builtin_bit_cast(unsigned long long, v.y));
 }
 
-// Sums over partials written inside the launch, in block_allsum3's order
-// (so each equals the chunked path's sum of the same array): out[0] over a,
-// out[1] over b (when b != nullptr), n entries each.
-__device__ __forceinline__ void cgp_allsum2(const double *__restrict__ a, const double *__restrict__ b, int n,
-                                            double (&out)[2], double *lds) {
-  double v[2] = {0.0, 0.0};
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    v[0] += cldd(a + i);
-    if (b != nullptr) v[1] += cldd(b + i);
-  }
-  const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+// The exchange at the end of a phase: everybody's two partial sums, and with
+// them the knowledge that everybody's vector entries are there.
+//
+// Few workgroups (CGP_DIRECT at most): a workgroup announces itself with its
+// sums, each as two 64-bit words of 32 value bits under a 32-bit tag (the
+// launch's epoch plus the phase number), and everybody polls all the words
+// until they carry the phase's tag: barrier and reduction in one round trip.
+// The words alternate between two sets: a workgroup writes a set again two
+// phases later, which it only reaches after everybody has announced the phase
+// between, that is, has read the set.  With 16 workgroups 4.6 us per phase; with
+// 512 every poll of everybody moves 8 MB and a solve takes 1.3 times as long
+// as with the counters below.
+//
+// More: the sums are stored, then an arrival is counted, and the first
+// wavefront polls the counters; the sums are loaded after that, beside the
+// vector entries of the next phase.  Arrivals are spread over CGP_NC counters
+// on separate 256-byte lines, so that no address takes every workgroup's
+// atomic.
+//
+// Why relaxed atomics order it: every value another workgroup reads was stored
+// with an agent-scope atomic store (written through to the agent's coherence
+// point) and is read with an agent-scope atomic load (which bypasses the XCD's
+// L2 and reads at that point).  s_waitcnt(0) holds each thread until its stores
+// are acknowledged, i.e. performed at agent scope; the workgroup barrier then
+// puts all of them before the announcement.  A reader issues its loads only
+// after its workgroup has seen every announcement (the loop exit and the
+// workgroup barrier order them after the polls).  A release / acquire pair
+// would give the same order with an L2 write-back and invalidate per phase;
+// with no exchanged data ever held in L2 they are not needed.
+constexpr uint32_t CGP_DIRECT = 128;
+constexpr int CGP_NC = 64;  // arrival counters: 8, 16, 32 and 64 measured alike
+
+// The set of a phase: tagged words first, bare sums (which could look like a
+// tag) behind them.
+__device__ __forceinline__ size_t cgp_set(uint32_t nblk, uint32_t tag) {
+  return nblk <= CGP_DIRECT ? (size_t)(tag & 1u) * 4 * nblk : 8 * CGP_DIRECT + (size_t)(tag & 1u) * 2 * nblk;
+}
+
+__device__ __forceinline__ void cgp_announce(double (&v)[2], unsigned long long *words, unsigned *bar, uint32_t nblk,
+                                             uint32_t tag, double *lds) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
 #pragma unroll
   for (int q = 0; q < 2; ++q) v[q] = wave_sum(v[q]);
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) lds[w * 3 + q] = v[q];
+  if (lane == 0) {
+    lds[w * 2] = v[0];
+    lds[w * 2 + 1] = v[1];
   }
+  const bool direct = nblk <= CGP_DIRECT;
+  unsigned long long *set = words + cgp_set(nblk, tag);
+  if (direct) __builtin_amdgcn_s_waitcnt(0);  // this thread's stores acknowledged
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    double t = 0.0;
-    for (int k = 0; k < nw; ++k) t += lds[k * 3 + q];
-    out[q] = t;
-  }
-  __syncthreads();
-}
-
-// Arrivals are spread over CGP_NC counters on separate 256-byte lines
-// (workgroup i counts on i mod CGP_NC), so that no single address takes
-// every workgroup's atomic; the first wavefront polls all of them at once.
-//
-// Why relaxed atomics order the exchange: every value another workgroup
-// reads was stored with an agent-scope atomic store (written through to the
-// agent's coherence point) and is read with an agent-scope atomic load
-// (which bypasses the XCD's L2 and reads at that point).  s_waitcnt(0)
-// holds each thread until its stores are acknowledged, i.e. performed at
-// agent scope; the workgroup barrier then puts all of them before the one
-// arrival increment.  A reader issues its data loads only after it has seen
-// the count reach the target (the loop exit and the workgroup barrier order
-// them after the poll).  So every data load is performed after every data
-// store it depends on, at the same coherence point.  A release / acquire pair
-// would give the same order with an L2 write-back and invalidate per barrier
-// (about 80 us each here); with no data ever held in L2 they are not needed.
-constexpr int CGP_NC = CGP_BAR_WORDS / 64;
-__device__ __forceinline__ bool cgp_barrier(unsigned *bar, unsigned target, int *fail, unsigned spin_max,
-                                            int *lds_ok) {
-  __builtin_amdgcn_s_waitcnt(0);  // this thread's stores acknowledged
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    if (lane == 0)
-      __hip_atomic_fetch_add(bar + (blockIdx.x % CGP_NC) * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int ok = 1;
-    unsigned spins = 0;
-    for (;;) {
-      unsigned v = lane < CGP_NC ? __hip_atomic_load(bar + lane * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-      v = wave_sum(v);
-      if (v >= target) break;
-      if (++spins > spin_max) {
-        ok = 0;
-        if (lane == 0) __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
+  const int q = (threadIdx.x >> 1) & 1;  // direct: thread 2 q + h announces half h of sum q
+  unsigned long long u = 0;
+  if (threadIdx.x < 4) {
+    double a = 0.0;
+    for (int j = 0; j < nw; ++j) a += lds[j * 2 + q];
+    u = __builtin_bit_cast(unsigned long long, a);
+    if (direct) {
+      const unsigned long long half = (threadIdx.x & 1) ? u >> 32 : u & 0xffffffffull;
+      xst(set + (size_t)threadIdx.x * nblk + blockIdx.x, (unsigned long long)tag << 32 | half);
+    } else if ((threadIdx.x & 1) == 0) {
+      xst(set + (size_t)q * nblk + blockIdx.x, u);
     }
-    if (lane == 0) *lds_ok = ok;
   }
+  if (direct) return;
+  __builtin_amdgcn_s_waitcnt(0);  // the vector entries and the sums, acknowledged together
   __syncthreads();
-  return *lds_ok != 0;
+  if (threadIdx.x == 0)
+    __hip_atomic_fetch_add(bar + (blockIdx.x % CGP_NC) * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename S, int RW, int PM>
-__global__ __launch_bounds__(512, 4) void k_cgnr_persistent(Geom g, int n, const S *__restrict__ L, CgPersist a) {
-  using C = float2;
+// Waits for every workgroup's announcement of `tag` (the phase-th of the
+// launch), calls pre() (which issues the next phase's loads) and sums the
+// values in block_allsum3's order, so that each sum equals the chunked path's
+// of the same array.  False when a wait gave up.
+template <typename F>
+__device__ __forceinline__ bool cgp_gather(const unsigned long long *words, unsigned *bar, uint32_t nblk,
+                                           uint32_t tag, uint32_t phase, double (&out)[2], double *lds, int *lds_ok,
+                                           int *fail, unsigned spin_max, F &&pre) {
+  const unsigned long long *set = words + cgp_set(nblk, tag);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+  double v[2] = {0.0, 0.0};
+  int ok = 1;
+  unsigned spins = 0;
+  if (nblk <= CGP_DIRECT) {
+    for (uint32_t i = threadIdx.x; i < nblk && ok; i += blockDim.x) {
+      unsigned long long u[4];
+      for (;;) {
+        bool all = true;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = xld(set + (size_t)q * nblk + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) all = all && (uint32_t)(u[q] >> 32) == tag;
+        if (all) break;
+        if (++spins > spin_max) {
+          ok = 0;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        v[q] += __builtin_bit_cast(double, (u[2 * q] & 0xffffffffull) | (u[2 * q + 1] << 32));
+    }
+  } else {
+    if (w == 0) {
+      const unsigned target = phase * nblk;
+      for (;;) {
+        unsigned c = lane < CGP_NC ? __hip_atomic_load(bar + lane * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        c = wave_sum(c);
+        if (c >= target) break;
+        if (++spins > spin_max) {
+          ok = 0;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      if (lane == 0) lds_ok[8] = ok;
+    }
+    __syncthreads();
+    ok = lds_ok[8];
+    if (ok) {
+      pre();
+      for (uint32_t i = threadIdx.x; i < nblk; i += blockDim.x) {
+        v[0] += __builtin_bit_cast(double, xld(set + i));
+        v[1] += __builtin_bit_cast(double, xld(set + nblk + i));
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) v[q] = wave_sum(v[q]);
+  ok = __all(ok);
+  if (lane == 0) {
+    lds[w * 2] = v[0];
+    lds[w * 2 + 1] = v[1];
+    lds_ok[w] = ok;
+    if (!ok) __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  __syncthreads();
+  int good = 1;
+  for (int k = 0; k < nw; ++k) good &= lds_ok[k];
+  if (nblk <= CGP_DIRECT && good) pre();
+  out[0] = out[1] = 0.0;
+  for (int k = 0; k < nw; ++k) {
+    out[0] += lds[k * 2];
+    out[1] += lds[k * 2 + 1];
+  }
+  return good != 0;
+}
+
+// The operator entries a thread holds in registers for the whole solve, where
+// they are half precision: converted at each use.  Left alone the compiler
+// converts them once, outside the iteration, and spills the doubled registers.
+template <typename S, int RW>
+__device__ __forceinline__ typename OpVec<S, RW>::V kept_packed(const typename OpVec<S, RW>::V &v) {
+  if constexpr (sizeof(S) == 4) {
+    struct W {
+      uint32_t w[RW];
+    } u = __builtin_bit_cast(W, v);
+#pragma unroll
+    for (int t = 0; t < RW; ++t) asm volatile("" : "+v"(u.w[t]));
+    return __builtin_bit_cast(typename OpVec<S, RW>::V, u);
+  } else {
+    return v;
+  }
+}
+
+template <typename R, typename S, int RW, int PM>
+__global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cgnr_persistent(Geom g, int n, const S *__restrict__ L,
+                                                            CgPersist<c_t<R>> a) {
+  using C = c_t<R>;
   using VT = typename OpVec<S, RW>::V;
-  __shared__ C vin[9 * COARSE_NMAX];
+  __shared__ C vin[9 * COARSE_NMAX], ploc[9 * COARSE_NMAX], rloc[9 * COARSE_NMAX];
   __shared__ C red[512 * RW];
   __shared__ C red2[CO_PARTS * COARSE_NMAX];
-  __shared__ double wred[8 * 4];
+  __shared__ double asum[16], gsum[2][16];
+  __shared__ int gok[2][9];
   __shared__ uint32_t nbs[9];
-  __shared__ int bar_ok;
   const uint32_t s = blockIdx.x, nblk = gridDim.x;
   const int tid = threadIdx.x;
   const int npr = n / RW, G = (int)blockDim.x / npr;
@@ -457,26 +554,30 @@ __global__ __launch_bounds__(512, 4) void k_cgnr_persistent(Geom g, int n, const
   }
   if (tid < 9) nbs[tid] = slot_site(g, s, tid);
   __syncthreads();
-  const double tol2b2 = a.cg[4] * a.cg[3];
-  unsigned round = 0;
-  double gam = 0.0;  // gamma_k = ||z_k||^2 of the current iteration
-  int k = 0, final_it = 0;
-  // a zero right-hand side was marked done before the launch (as the chunks
-  // see it): no iteration, e stays zero
-  const bool nothing = a.done[0] != 0;
+  // where this thread's staged entries tid and tid + blockDim come from
+  const int i0 = tid, i1 = tid + (int)blockDim.x;  // 9 n <= 2 blockDim
+  const bool h0 = i0 < nP, h1 = i1 < nP;
+  const uint32_t o0 = h0 ? nbs[i0 / n] * n + i0 % n : 0, o1 = h1 ? nbs[i1 / n] * n + i1 % n : 0;
+  const bool neg0 = i0 % n >= half, neg1 = i1 % n >= half;
+  const uint32_t own = s * n + tid;
+  unsigned *bar = a.bar + (size_t)(a.launch & 1u) * CGP_NC * 64;
+  if (s == 0 && tid < CGP_NC)  // the next launch's counters
+    __hip_atomic_store(a.bar + (size_t)((a.launch + 1) & 1u) * CGP_NC * 64 + tid * 64, 0u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
   // rows of this workgroup times the staged vector, summed over the groups in
   // the fixed two-stage order of k_coarse; returns the row sum (tid < n)
   auto apply = [&]() -> C {
+    __syncthreads();
     C acc[RW];
 #pragma unroll
-    for (int t = 0; t < RW; ++t) acc[t] = make_float2(0.f, 0.f);
+    for (int t = 0; t < RW; ++t) acc[t] = mk<C>(0, 0);
 #pragma unroll
     for (int q = 0; q < PM; ++q) {
       const int p = grp + q * G;
       if (on && p < nP) {
         const C x = vin[p];
         C o[RW];
-        OpVec<S, RW>::get(lv[q], o);
+        OpVec<S, RW>::get(kept_packed<S, RW>(lv[q]), o);
 #pragma unroll
         for (int t = 0; t < RW; ++t) acc[t] = cfma(o[t], x, acc[t]);
       }
@@ -487,12 +588,12 @@ __global__ __launch_bounds__(512, 4) void k_cgnr_persistent(Geom g, int n, const
     if (tid < n * CO_PARTS) {
       const int i = tid % n, part = tid / n;
       const int ipr = i / RW, sub = i % RW;
-      C sum = make_float2(0.f, 0.f);
+      C sum = mk<C>(0, 0);
       for (int q = part; q < G; q += CO_PARTS) sum = cadd(sum, red[(q * npr + ipr) * RW + sub]);
       red2[part * COARSE_NMAX + i] = sum;
     }
     __syncthreads();
-    C sum = make_float2(0.f, 0.f);
+    C sum = mk<C>(0, 0);
     if (tid < n) {
       sum = red2[tid];
 #pragma unroll
@@ -500,127 +601,142 @@ __global__ __launch_bounds__(512, 4) void k_cgnr_persistent(Geom g, int n, const
     }
     return sum;
   };
-  for (; !nothing;) {
-    // ---- phase 1: convergence test of the last update, p = z + beta p_old, w = A p
-    float2 *pn = a.p[k & 1];
-    const float2 *po = a.p[(k + 1) & 1];
-    // ||r||^2 of the last update and gamma_k = ||z_k||^2; gamma_{k-1} is
-    // the sum of the same array the previous phase 1 made (the chunked path
-    // sums it again, to the same value)
-    double sums[2] = {0.0, 0.0};
-    if (k > 0) cgp_allsum2(a.pr, a.pz[k & 1], (int)nblk, sums, wred);
-    if ((k > 0 && !(sums[0] > tol2b2)) || k >= a.maxit) {
+  // r = b, p = 0, e = 0
+  double sq = 0.0;
+  {
+    const C b0 = h0 ? a.b[o0] : mk<C>(0, 0), b1 = h1 ? a.b[o1] : mk<C>(0, 0);
+    if (h0) {
+      rloc[i0] = b0;
+      ploc[i0] = mk<C>(0, 0);
+      vin[i0] = neg0 ? mk<C>(-b0.x, -b0.y) : b0;
+    }
+    if (h1) {
+      rloc[i1] = b1;
+      ploc[i1] = mk<C>(0, 0);
+      vin[i1] = neg1 ? mk<C>(-b1.x, -b1.y) : b1;
+    }
+    if (tid < n) sq = (double)b0.x * b0.x + (double)b0.y * b0.y;
+  }
+  C e = mk<C>(0, 0), x0, x1;
+  double sums[2], gam = 0.0, tol2b2 = 0.0;  // gam: ||z_k||^2
+  int k = 0, final_it = 0;
+  unsigned phase = 0;
+  for (;;) {
+    // ---- z = A^dag r; ||z||^2 and ||r||^2 (of the update just made; at first ||b||^2)
+    {
+      C zv = apply();
+      double v[2] = {0.0, sq};
+      if (tid < n) {
+        if (tid >= half) zv = mk<C>(-zv.x, -zv.y);
+        cst(a.z + own, zv);
+        v[0] = (double)zv.x * zv.x + (double)zv.y * zv.y;
+      }
+      ++phase;
+      cgp_announce(v, a.words, bar, nblk, a.epoch + phase, asum);
+    }
+    if (!cgp_gather(a.words, bar, nblk, a.epoch + phase, phase, sums, gsum[0], gok[0], a.fail, a.spin, [&]() {
+          x0 = cld(a.z + o0);
+          x1 = h1 ? cld(a.z + o1) : x0;
+        }))
+      break;
+    R beta = 0;
+    if (phase == 1) {
+      tol2b2 = a.tol2 * sums[1];
+      if (!(sums[1] > 0.0)) break;  // zero right-hand side: no iteration, e = 0
+    } else {
+      if (!(sums[1] > tol2b2)) {
+        final_it = k;
+        break;
+      }
+      beta = gam > 0.0 ? (R)(sums[0] / gam) : (R)0;
+    }
+    gam = sums[0];
+    if (k >= a.maxit) {
       final_it = k;
       break;
     }
-    const float beta = (k > 0 && gam > 0.0) ? (float)(sums[1] / gam) : 0.f;
-    if (k > 0) gam = sums[1];
-    for (int idx = tid; idx < nP; idx += blockDim.x) {
-      const int slot = idx / n, j = idx - slot * n;
-      const size_t o = (size_t)nbs[slot] * n + j;
-      const C v = cfma(make_float2(beta, 0.f), cld(po + o), cld(a.z + o));
-      if (slot == 0) cst(pn + o, v);
-      vin[idx] = v;
-    }
-    __syncthreads();
+    // ---- p = z + beta p_old, w = A p; ||w||^2
+    if (h0) vin[i0] = ploc[i0] = cfma(mk<C>(beta, 0), ploc[i0], x0);
+    if (h1) vin[i1] = ploc[i1] = cfma(mk<C>(beta, 0), ploc[i1], x1);
     {
       const C wv = apply();
-      double t2 = 0.0;
+      double v[2] = {0.0, 0.0};
       if (tid < n) {
-        cst(a.w + (size_t)s * n + tid, wv);
-        t2 = (double)wv.x * wv.x + (double)wv.y * wv.y;
+        cst(a.w + own, wv);
+        v[0] = (double)wv.x * wv.x + (double)wv.y * wv.y;
       }
-      double v4[4] = {0.0, 0.0, t2, 0.0};
-      block_sum<4>(v4, wred);
-      if (tid == 0) cstd(a.pw + s, v4[2]);
+      ++phase;
+      cgp_announce(v, a.words, bar, nblk, a.epoch + phase, asum);
     }
-    if (!cgp_barrier(a.bar, ++round * nblk, a.fail, a.spin, &bar_ok)) {
-      final_it = k;
+    if (!cgp_gather(a.words, bar, nblk, a.epoch + phase, phase, sums, gsum[1], gok[1], a.fail, a.spin, [&]() {
+          x0 = cld(a.w + o0);
+          x1 = h1 ? cld(a.w + o1) : x0;
+        }))
       break;
-    }
-    // ---- phase 2: r = r_old - alpha w, e += alpha p, z = A^dag r
-    const float2 *ro = a.r[k & 1];
-    float2 *rn = a.r[(k + 1) & 1];
-    // ||w||^2 (and gamma_0 at the first iteration)
-    cgp_allsum2(a.pw, k == 0 ? a.pz[0] : nullptr, (int)nblk, sums, wred);
-    if (k == 0) gam = sums[1];
     if (!(sums[0] > 0.0)) {
       final_it = k + 1;
       break;
     }
-    const float alpha = (float)(gam / sums[0]);
-    double own_sq = 0.0;
-    for (int idx = tid; idx < nP; idx += blockDim.x) {
-      const int slot = idx / n, j = idx - slot * n;
-      const size_t o = (size_t)nbs[slot] * n + j;
-      C v = cfma(make_float2(-alpha, 0.f), cld(a.w + o), cld(ro + o));
-      if (slot == 0) {
-        cst(rn + o, v);
-        a.e[o] = cfma(make_float2(alpha, 0.f), cld(pn + o), a.e[o]);
-        own_sq += (double)v.x * v.x + (double)v.y * v.y;
-      }
-      if (j >= half) v = make_float2(-v.x, -v.y);
-      vin[idx] = v;
-    }
-    __syncthreads();
-    {
-      C zv = apply();
-      double t2 = 0.0;
+    // ---- r = r_old - alpha w, e += alpha p
+    const R alpha = (R)(gam / sums[0]);
+    if (h0) {
+      const C v = cfma(mk<C>(-alpha, 0), x0, rloc[i0]);
+      rloc[i0] = v;
+      vin[i0] = neg0 ? mk<C>(-v.x, -v.y) : v;
       if (tid < n) {
-        if (tid >= half) zv = make_float2(-zv.x, -zv.y);
-        cst(a.z + (size_t)s * n + tid, zv);
-        t2 = (double)zv.x * zv.x + (double)zv.y * zv.y;
+        e = cfma(mk<C>(alpha, 0), ploc[tid], e);
+        sq = (double)v.x * v.x + (double)v.y * v.y;
       }
-      double v4[4] = {0.0, 0.0, t2, own_sq};
-      block_sum<4>(v4, wred);
-      if (tid == 0) {
-        cstd(a.pz[(k + 1) & 1] + s, v4[2]);
-        cstd(a.pr + s, v4[3]);
-      }
+    }
+    if (h1) {
+      const C v = cfma(mk<C>(-alpha, 0), x1, rloc[i1]);
+      rloc[i1] = v;
+      vin[i1] = neg1 ? mk<C>(-v.x, -v.y) : v;
     }
     ++k;
-    if (!cgp_barrier(a.bar, ++round * nblk, a.fail, a.spin, &bar_ok)) {
-      final_it = k;
-      break;
-    }
   }
-  if (s == 0 && tid == 0) {
-    a.it[0] = final_it;
-    a.it[1] = final_it;
-    a.done[0] = 1;
-  }
+  if (tid < n) a.e[own] = e;
+  if (s == 0 && tid < 2) __hip_atomic_store(a.it + tid, final_it, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <typename S>
-hipError_t cgnr_persistent(const Geom &g, int n, const S *L, const CgPersist &a, hipStream_t st) {
+template <typename R, typename S>
+hipError_t cgnr_persistent(const Geom &g, int n, const S *L, const CgPersist<c_t<R>> &a, hipStream_t st) {
   const int rs = coarse_split(n, g.V);
   if (rs != 1 || n > COARSE_NMAX) return hipErrorInvalidValue;
   const int th = coarse_threads(n, g.V);
-  const bool rw4 = sizeof(S) == 4 && n % 4 == 0;
-  const int RW = sizeof(S) == 4 ? (rw4 ? 4 : 2) : 2;
-  const int G = th / (n / RW);
-  if ((9 * n + G - 1) / G > CGP_PMAX || th > 512 || 9 * n > 2 * th) return hipErrorInvalidValue;
-  CgPersist args = a;
+  // rows per thread as of k_coarse in this storage
+  const int RW = sizeof(S) == 16 ? 1 : sizeof(S) == 4 && n % 4 == 0 ? 4 : 2;
+  if (n % RW != 0) return hipErrorInvalidValue;
+  const int G = th / (n / RW), pm = (9 * n + G - 1) / G;
+  if (pm > CGP_PMAX || th > 512 || 9 * n > 2 * th || n * CO_PARTS > th) return hipErrorInvalidValue;
+  CgPersist<c_t<R>> args = a;
   Geom gg = g;
   const S *LL = L;
   int nn = n;
   void *kargs[] = {&gg, &nn, &LL, &args};
   // entries per thread decide the register array: 8 where they fit
-  const bool p8 = (9 * n + G - 1) / G <= 8;
+  const bool p8 = pm <= 8;
   const void *fn;
   if constexpr (sizeof(S) == 4) {
-    if (rw4 && !p8) return hipErrorInvalidValue;  // 16 four-row entries would spill
-    if (rw4) fn = reinterpret_cast<const void *>(&k_cgnr_persistent<S, 4, 8>);
-    else fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<S, 2, 8>)
-                 : reinterpret_cast<const void *>(&k_cgnr_persistent<S, 2, 16>);
+    if (RW == 4 && !p8) return hipErrorInvalidValue;  // 16 four-row entries would spill
+    if (RW == 4) fn = reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 4, 8>);
+    else fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 8>)
+                 : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 16>);
+  } else if constexpr (sizeof(S) == 8) {
+    fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 8>)
+            : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 16>);
   } else {
-    fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<S, 2, 8>)
-            : reinterpret_cast<const void *>(&k_cgnr_persistent<S, 2, 16>);
+    fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 1, 8>)
+            : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 1, 16>);
   }
   return hipLaunchCooperativeKernel(fn, dim3(g.V), dim3(th), kargs, 0, st);
 }
-template hipError_t cgnr_persistent<chalf>(const Geom &, int, const chalf *, const CgPersist &, hipStream_t);
-template hipError_t cgnr_persistent<float2>(const Geom &, int, const float2 *, const CgPersist &, hipStream_t);
+template hipError_t cgnr_persistent<float, chalf>(const Geom &, int, const chalf *, const CgPersist<float2> &,
+                                                  hipStream_t);
+template hipError_t cgnr_persistent<float, float2>(const Geom &, int, const float2 *, const CgPersist<float2> &,
+                                                   hipStream_t);
+template hipError_t cgnr_persistent<double, double2>(const Geom &, int, const double2 *, const CgPersist<double2> &,
+                                                     hipStream_t);
 
 // ------------------------------------------------------------ matrix cores
 typedef float floatx4 __attribute__((ext_vector_type(4)));

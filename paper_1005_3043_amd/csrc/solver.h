@@ -344,13 +344,15 @@ struct mg_ctx {
   int vgraph_on = 0;                          // set by the outer solver around its cycles
   mg::DevBuf<double2> csc;
   mg::DevBuf<int> done, it;
-  // whole-solve cooperative CGNR (one RHS): barrier counter, give-up flag,
-  // on/off, and per (level, precision class) whether the launch was refused
+  // whole-solve cooperative CGNR (one RHS): exchange words and arrival
+  // counters, the epoch of the words' tags, the launch number, on/off, and per
+  // (level, precision class) whether the launch was refused
+  mg::DevBuf<unsigned long long> cgp_words;
   mg::DevBuf<unsigned> cgp_bar;
-  mg::DevBuf<int> cgp_fail;
+  unsigned cgp_epoch = 1, cgp_launch = 0;
   int cg_persist = 1;
   int gcr_fuse = 1;  // mg_set_gcr_fusion
-  unsigned cgp_spin = 1u << 20;  // barrier polls before a wait gives up
+  unsigned cgp_spin = 1u << 20;  // polls before a wait gives up
   int cgp_off[MG_MAX_LEVELS][3] = {};
   int *h_done = nullptr;   // pinned host mirrors
   double *h_rr = nullptr;
