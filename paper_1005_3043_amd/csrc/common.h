@@ -212,14 +212,14 @@ __device__ __forceinline__ void store_site(h16 *__restrict__ f, uint32_t s, C (&
 #pragma unroll
   for (int c = 0; c < 12; ++c) m = fmaxf(m, fmaxf(fabsf((float)v[c].x), fabsf((float)v[c].y)));
   const float inv = m > 0.f ? 1.0f / m : 0.f;
+  typedef _Float16 half2 __attribute__((ext_vector_type(2)));
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
-    h16 e;
-    e.x = (_Float16)((float)v[c].x * inv);
-    e.y = (_Float16)((float)v[c].y * inv);
+    // a vector, not h16: the struct's bits would pass through memory
+    const half2 e = {(_Float16)((float)v[c].x * inv), (_Float16)((float)v[c].y * inv)};
     v[c] = mk<C>((float)e.x * m, (float)e.y * m);
     if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(float, e), (float *)&f[fidx(s, c, 13)]);
-    else f[fidx(s, c, 13)] = e;
+    else *(float *)&f[fidx(s, c, 13)] = __builtin_bit_cast(float, e);
   }
   const h16 ms = __builtin_bit_cast(h16, m);
   if constexpr (NT) __builtin_nontemporal_store(m, (float *)&f[fidx(s, 12, 13)]);
@@ -250,18 +250,25 @@ __host__ __device__ __forceinline__ Coords decode(const Geom &g, uint32_t s) {
 }
 
 // Site index of the forward (+mu) neighbour, periodic.
-__host__ __device__ __forceinline__ uint32_t nbr_fwd(const Geom &g, uint32_t s, const Coords &k, int mu) {
-  if (k.o[mu] + 1 < g.b[mu]) return s + g.Sl[mu];
+// (o, c: the site's coordinates o_mu in and c_mu of its aggregate.)
+__host__ __device__ __forceinline__ uint32_t nbr_fwd(const Geom &g, uint32_t s, int o, int c, int mu) {
+  if (o + 1 < g.b[mu]) return s + g.Sl[mu];
   int64_t t = (int64_t)s - (int64_t)(g.b[mu] - 1) * g.Sl[mu];
-  t += (k.c[mu] + 1 < g.C[mu]) ? (int64_t)g.Sb[mu] : -(int64_t)(g.C[mu] - 1) * g.Sb[mu];
+  t += (c + 1 < g.C[mu]) ? (int64_t)g.Sb[mu] : -(int64_t)(g.C[mu] - 1) * g.Sb[mu];
   return (uint32_t)t;
 }
+__host__ __device__ __forceinline__ uint32_t nbr_fwd(const Geom &g, uint32_t s, const Coords &k, int mu) {
+  return nbr_fwd(g, s, k.o[mu], k.c[mu], mu);
+}
 // Site index of the backward (-mu) neighbour, periodic.
-__host__ __device__ __forceinline__ uint32_t nbr_bwd(const Geom &g, uint32_t s, const Coords &k, int mu) {
-  if (k.o[mu] > 0) return s - g.Sl[mu];
+__host__ __device__ __forceinline__ uint32_t nbr_bwd(const Geom &g, uint32_t s, int o, int c, int mu) {
+  if (o > 0) return s - g.Sl[mu];
   int64_t t = (int64_t)s + (int64_t)(g.b[mu] - 1) * g.Sl[mu];
-  t += (k.c[mu] > 0) ? -(int64_t)g.Sb[mu] : (int64_t)(g.C[mu] - 1) * g.Sb[mu];
+  t += (c > 0) ? -(int64_t)g.Sb[mu] : (int64_t)(g.C[mu] - 1) * g.Sb[mu];
   return (uint32_t)t;
+}
+__host__ __device__ __forceinline__ uint32_t nbr_bwd(const Geom &g, uint32_t s, const Coords &k, int mu) {
+  return nbr_bwd(g, s, k.o[mu], k.c[mu], mu);
 }
 // Lexicographic (canonical) index of an internal site.
 __host__ __device__ __forceinline__ uint32_t canon_index(const Geom &g, const Coords &k) {

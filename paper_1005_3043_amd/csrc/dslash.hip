@@ -6,14 +6,12 @@
 // The spin projection (wilson_site.h) reduces each hop to a half spinor and
 // two SU(3) mat-vecs: 1320 flops per site for all eight hops.
 //
-// One thread per site of the site-blocked, tile-interleaved layout (two
-// right-hand sides per thread when there are several).  The loop over mu is
-// rolled (wave-uniform): both hops of one direction issue their 42 (or 36
-// with compressed links) loads together, then compute, which doubles the
-// loads in flight per wave compared with one hop at a time.  Links are either stored in full (9
-// complex) or as their first two rows (6 complex, NL = 6); the third row of an
-// SU(3) matrix is the complex conjugate of the cross product of the first two,
-// which trades 42 flops per link for a third less link traffic.
+// One thread per site of the site-blocked, tile-interleaved layout (two or
+// three right-hand sides per thread when there are several).  The loop over mu
+// is rolled (wave-uniform).  Links are either stored in full (9 complex) or as
+// their first two rows (6 complex, NL = 6); the third row of an SU(3) matrix is
+// the complex conjugate of the cross product of the first two, which trades 42
+// flops per link for a third less link traffic.
 #include <type_traits>
 
 #include "kernels.h"
@@ -38,49 +36,41 @@ __device__ __forceinline__ void load_link_t(C (&u)[9], const S *__restrict__ U, 
   if constexpr (NL == 6) reconstruct_row2(u);
 }
 
-// Full stencil at one site: res = D psi at s, ctr = psi(s).  The input
-// spinors may be stored in a narrower type TI than the arithmetic type C.
-template <int NL, typename C, typename S, typename TI>
-__device__ __forceinline__ void dslash_site(C (&res)[12], C (&ctr)[12], const Geom &g, uint32_t s,
-                                                     const S *__restrict__ U, const TI *__restrict__ in,
-                                                     decltype(C::x) diag) {
-  using R = decltype(C::x);
-  const Coords k = decode(g, s);
-  C acc[12];
+// A 256-site workgroup's copy of its own input, each thread one site, in the
+// storage type and the layout of the field.
+template <typename TI> __device__ __forceinline__ void stage_sites(TI *sh, const TI *__restrict__ in, uint32_t s) {
+  constexpr int NS = SiteSlots<TI>::n;
 #pragma unroll
-  for (int i = 0; i < 12; ++i) acc[i] = mk<C>(0, 0);
-#pragma unroll 1
-  for (int mu = 0; mu < 4; ++mu) {
-    C pf[12], pb[12], uf[9], ub[9];
-    const uint32_t sf = nbr_fwd(g, s, k, mu), sb = nbr_bwd(g, s, k, mu);
-    R ef = 1, eb = 1;
-    if (mu == 3 && g.antiperiodic) {
-      if (k.o[3] == g.b[3] - 1 && k.c[3] == g.C[3] - 1) ef = -1;
-      if (k.o[3] == 0 && k.c[3] == 0) eb = -1;
-    }
-    load_site(pf, in, sf);
-    load_site(pb, in, sb);
-    load_link_t<NL>(uf, U, mu, s);
-    load_link_t<NL>(ub, U, mu, sb);
-    hop_dispatch<true>(mu, acc, pf, uf, ef);
-    hop_dispatch<false>(mu, acc, pb, ub, eb);
-  }
-  load_site(ctr, in, s);
-#pragma unroll
-  for (int i = 0; i < 12; ++i) {
-    res[i].x = fma(diag, ctr[i].x, (R)-0.5 * acc[i].x);
-    res[i].y = fma(diag, ctr[i].y, (R)-0.5 * acc[i].y);
-  }
+  for (int c = 0; c < NS; ++c) sh[fidx(threadIdx.x, c, NS)] = in[fidx(s, c, NS)];
 }
 
 // The stencil at one site for K right-hand sides (input stride vs between
 // them): each direction's two links are loaded once and applied to all K.
 // Only the first kv are distinct; the spare slots repeat the last of them.
+//
+// Bound by the bytes that miss L2: the wavefronts in flight on an XCD hold
+// more spinors and links than its 4 MB, so a site's spinor was fetched again
+// by each hop that read it (4.1 times, 12 FP32 right-hand sides on 32^3 x 64).
+// The workgroup's own 256 sites are therefore copied to LDS once (sh), and a
+// hop that stays inside them reads there: with 4^4 aggregates two thirds of
+// all hops.  The choice is one address select per hop in front of flat loads;
+// loads in two divergent branches measured 2.42 ms, one select 2.22, no copy
+// 2.38.  Per launch, before / after: one right-hand side FP64 494 / 386 us,
+// FP32 264 / 236, FP16 class 162 / 139; twelve FP64 4.49 / 3.99 ms, FP32 2.39
+// / 2.18, FP16 class 1.67 / 1.58, the MR q-recursion forms 3.29 / 3.03 and
+// 2.32 / 2.21.  On 16^3 x 32 one FP32 right-hand side took 27.7 us with the
+// coordinates in an indexed array (memory), 15.5 with selects.
 template <int K, int NL, typename C, typename S, typename TI>
 __device__ __forceinline__ void dslash_site_k(C (&res)[K][12], C (&ctr)[K][12], const Geom &g, uint32_t s,
                                               const S *__restrict__ U, const TI *__restrict__ in, size_t vs, int kv,
-                                              decltype(C::x) diag) {
+                                              decltype(C::x) diag, const TI *sh) {
   using R = decltype(C::x);
+  constexpr int NS = SiteSlots<TI>::n;
+  // component c at 64 c behind this, in the workgroup's copy or in memory
+  auto site = [&](int k, uint32_t t) -> const TI * {
+    return (t ^ s) < 256 ? sh + k * 256 * NS + fidx(t & 255u, 0, NS)
+                         : in + (size_t)(k < kv ? k : kv - 1) * vs + fidx(t, 0, NS);
+  };
   const Coords kk = decode(g, s);
   C acc[K][12];
 #pragma unroll
@@ -89,7 +79,10 @@ __device__ __forceinline__ void dslash_site_k(C (&res)[K][12], C (&ctr)[K][12], 
     for (int i = 0; i < 12; ++i) acc[k][i] = mk<C>(0, 0);
 #pragma unroll 1
   for (int mu = 0; mu < 4; ++mu) {
-    const uint32_t sf = nbr_fwd(g, s, kk, mu), sb = nbr_bwd(g, s, kk, mu);
+    // selects, not an indexed array (which would live in memory)
+    const int o = mu == 0 ? kk.o[0] : mu == 1 ? kk.o[1] : mu == 2 ? kk.o[2] : kk.o[3];
+    const int cc = mu == 0 ? kk.c[0] : mu == 1 ? kk.c[1] : mu == 2 ? kk.c[2] : kk.c[3];
+    const uint32_t sf = nbr_fwd(g, s, o, cc, mu), sb = nbr_bwd(g, s, o, cc, mu);
     R ef = 1, eb = 1;
     if (mu == 3 && g.antiperiodic) {
       if (kk.o[3] == g.b[3] - 1 && kk.c[3] == g.C[3] - 1) ef = -1;
@@ -100,20 +93,20 @@ __device__ __forceinline__ void dslash_site_k(C (&res)[K][12], C (&ctr)[K][12], 
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       C p[12];
-      load_site(p, in + (size_t)(k < kv ? k : kv - 1) * vs, sf);
+      load_site(p, site(k, sf), 0);
       hop_dispatch<true>(mu, acc[k], p, u, ef);
     }
     load_link_t<NL>(u, U, mu, sb);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       C p[12];
-      load_site(p, in + (size_t)(k < kv ? k : kv - 1) * vs, sb);
+      load_site(p, site(k, sb), 0);
       hop_dispatch<false>(mu, acc[k], p, u, eb);
     }
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    load_site(ctr[k], in + (size_t)(k < kv ? k : kv - 1) * vs, s);
+    load_site(ctr[k], sh + k * 256 * NS, s & 255u);
 #pragma unroll
     for (int i = 0; i < 12; ++i) {
       res[k][i].x = fma(diag, ctr[k][i].x, (R)-0.5 * acc[k][i].x);
@@ -154,37 +147,6 @@ __device__ __forceinline__ uint32_t visit_pos(uint32_t q, uint32_t nblk, const G
 __device__ __forceinline__ uint32_t visit_block(uint32_t bid, uint32_t nblk, const Geom &g, uint32_t per) {
   return visit_pos(xcd_remap(bid, nblk), nblk, g, per);
 }
-
-// 64-site tile (one wavefront) that wave w of workgroup bid (of nblk, with
-// wpb waves each) visits.  With 4^4 aggregates a tile is the 4 x 4 x 4 cube
-// at one time slice o_t of an aggregate; the tiles of XCD k are those of
-// its z layers, walked x fastest, then y, then z, then the site time 4 c_t +
-// o_t, so that a tile's time neighbours are one x-y layer of tiles away
-// (1.6 MB of spinors and links for two FP32 right-hand sides on 32^3 x 64,
-// against 6.3 MB for the layer of whole aggregates, more than an XCD's 4 MB
-// L2): on 32^3 x 64 with 12 right-hand sides 2 % faster than visiting whole
-// aggregates, 3-4 % fewer bytes fetched in FP32 and FP16.  Other shapes
-// take visit_block's order, a wave per tile of each block.
-__device__ __forceinline__ uint32_t visit_tile(uint32_t bid, uint32_t nblk, uint32_t w, uint32_t wpb,
-                                               const Geom &g) {
-  const uint32_t C0 = (uint32_t)g.C[0], C1 = (uint32_t)g.C[1], C2 = (uint32_t)g.C[2];
-  const uint32_t ntile = nblk * wpb;
-  if (g.vb == 256 && g.b[0] == 4 && g.b[1] == 4 && g.b[2] == 4 && (nblk & 7u) == 0 &&
-      C2 % 8 == 0 && ntile == g.Vc * 4u) {
-    const uint32_t q = xcd_remap(bid, nblk) * wpb + w;
-    const uint32_t per_xcd = ntile >> 3, xcd = q / per_xcd;
-    uint32_t r = q - xcd * per_xcd;
-    const uint32_t cx = r % C0;
-    r /= C0;
-    const uint32_t cy = r % C1;
-    r /= C1;
-    const uint32_t nz = C2 >> 3, czl = r % nz, T = r / nz;
-    const uint32_t cz = xcd * nz + czl, ct = T >> 2, ot = T & 3u;
-    return (cx + C0 * (cy + C1 * (cz + C2 * ct))) * 4u + ot;
-  }
-  return visit_block(bid, nblk, g, 64 * wpb) * wpb + w;
-}
-
 
 // Minimum waves per SIMD requested from the register allocator (0 = none).
 #ifndef MG_DSLASH_WAVES_F64
@@ -234,11 +196,15 @@ __global__ __launch_bounds__(256, dslash_waves<R>()) void k_dslash(Geom g, const
   in += (size_t)blockIdx.y * site_slots<TI>() * g.Vpad;
   const size_t off = (size_t)blockIdx.y * site_slots<TO>() * g.Vpad;
   out += off;
-  const uint32_t s = visit_tile(blockIdx.x, gridDim.x, threadIdx.x >> 6, blockDim.x >> 6, g) * 64 + (threadIdx.x & 63);
+  const uint32_t s = visit_block(blockIdx.x, gridDim.x, g, 256) * 256 + threadIdx.x;
+  __shared__ TI sh[256 * SiteSlots<TI>::n];
+  stage_sites(sh, in, s < g.V ? s : g.V - 1);
+  __syncthreads();
   double red[3] = {0.0, 0.0, 0.0};
   if (s < g.V) {
-    C res[12], ctr[12];
-    dslash_site<NL, C>(res, ctr, g, s, U, in, diag);
+    C res1[1][12], ctr1[1][12];
+    dslash_site_k<1, NL, C>(res1, ctr1, g, s, U, in, 0, 1, diag, sh);
+    C(&res)[12] = res1[0], (&ctr)[12] = ctr1[0];
     if constexpr (MODE == DS_RESID) {
       C bb[12];
       load_site_nt(bb, b + off, s);
@@ -275,13 +241,11 @@ __global__ __launch_bounds__(256, dslash_waves<R>()) void k_dslash(Geom g, const
 // Several right-hand sides: K per thread (256-site workgroups), so that
 // each direction's links are loaded once for all K; the workgroups of one
 // group of K right-hand sides cover the lattice, grid.y = groups (K from
-// mrhs_k below).  K = 2:
-// on 32^3 x 64 with 12 right-hand sides, per right-hand side FP64 0.40 ms
-// (one per thread: 0.47 ms), FP32 0.214 ms (0.231), FP16-stored links 0.195
-// ms (0.198); K = 4 is slower in FP32 (0.248 ms: one wave per SIMD), and so
-// is running the groups of one block back to back on an XCD (links from L2,
-// but the spinor neighbours further apart: FP32 0.228 ms, more traffic).  A ragged last group repeats its last
-// right-hand side in the spare slots and stores only the valid ones.
+// take_three below).  K = 2 against one per thread, 12 right-hand sides on
+// 32^3 x 64: FP32 2.25 / 2.60 ms.  Running the groups of one block back to
+// back on an XCD is slower (links from L2, but the spinor neighbours further
+// apart).  A ragged last group repeats its last right-hand side in the spare
+// slots and stores only the valid ones.
 // Tile blocks per chunk of the right-hand-side-group order below (0: the
 // groups one after another over the whole lattice).  On 32^3 x 64 with 12
 // right-hand sides, 512 blocks (16 chunks, 25 MB of FP32 links each):
@@ -315,13 +279,19 @@ __global__ __launch_bounds__(256, dslash_waves<R>()) void k_dslash_rb(Geom g, co
   const uint32_t slot = bid, nslot = gridDim.x;
   const int kv = nrhs - r0 < K ? nrhs - r0 : K;
   const size_t vsi = (size_t)site_slots<TI>() * g.Vpad, vso = (size_t)site_slots<TO>() * g.Vpad;
-  const uint32_t s = visit_tile(bid, gridDim.x, threadIdx.x >> 6, blockDim.x >> 6, g) * 64 + (threadIdx.x & 63);
+  const uint32_t s = visit_block(bid, gridDim.x, g, 256) * 256 + threadIdx.x;
+  __shared__ TI sh[K * 256 * SiteSlots<TI>::n];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    stage_sites(sh + k * 256 * SiteSlots<TI>::n, in + (size_t)(r0 + (k < kv ? k : kv - 1)) * vsi,
+                s < g.V ? s : g.V - 1);
+  __syncthreads();
   double red[K][3];
 #pragma unroll
   for (int k = 0; k < K; ++k) red[k][0] = red[k][1] = red[k][2] = 0.0;
   if (s < g.V) {
     C res[K][12], ctr[K][12];
-    dslash_site_k<K, NL, C>(res, ctr, g, s, U, in + (size_t)r0 * vsi, vsi, kv, diag);
+    dslash_site_k<K, NL, C>(res, ctr, g, s, U, in + (size_t)r0 * vsi, vsi, kv, diag, sh);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (k >= kv) break;
@@ -366,50 +336,56 @@ __global__ __launch_bounds__(256, dslash_waves<R>()) void k_dslash_rb(Geom g, co
 }
 
 // Right-hand sides per thread of the multi-RHS stencil: each link is loaded
-// once per group.  Three for binary16 spinors (about 240 registers, two
-// waves per SIMD as with two; the links are read four times per 12-RHS
-// launch instead of six: 1.82 -> 1.72 ms plain, 2.55 -> 2.43 ms in the MR
-// q-recursion form on 32^3 x 64) and for the outer method's FP64 operator on
-// FP32-stored vectors (256 registers, no spill, one wave per SIMD: 7 % less
-// time per step in that class), two otherwise (FP32 spinors: 2.51 against
-// 2.58 ms with three, 3.40 against 3.38 ms; FP64 spinors spill with three).
-template <typename R, typename TI> constexpr int mrhs_k() {
-  return ((sizeof(R) == 4 && std::is_same<TI, h16>::value) || (sizeof(R) == 8 && std::is_same<TI, float2>::value))
-             ? 3
-             : 2;
+// once per group, and a ragged last group computes its spare slots.  Three
+// where that computes no more slots than two would, two otherwise (both at
+// two waves per SIMD).  32^3 x 64, two / three: 12 right-hand sides FP32 2.25
+// / 2.18 ms, binary16 spinors 1.68 / 1.58 ms; four right-hand sides FP32 0.77
+// / 0.99 ms, binary16 0.59 / 0.73 ms.  FP64 spinors spill with three; FP64
+// arithmetic on FP32-stored vectors (256 registers, no spill, one wave per
+// SIMD) follows the rule.
+template <typename R, typename TI> bool take_three(int nrhs) {
+  return !(sizeof(R) == 8 && std::is_same<TI, double2>::value) && (nrhs + 2) / 3 * 3 <= (nrhs + 1) / 2 * 2;
 }
 
 int dslash_blocks(const Geom &g) { return div_up(g.V, 256); }
 int dslash_partials(const Geom &g, int) { return dslash_blocks(g); }
 
+template <typename R, int NL, typename S, int K, typename TI, typename TO>
+static hipError_t launch_rb(const Geom &g, const S *U, const TI *in, TO *out, const TO *b, double diag, int nrhs,
+                            DslashMode mode, double *partials, hipStream_t st, MrqArgs<TO> mq) {
+  dim3 grid(dslash_blocks(g), (nrhs + K - 1) / K);
+  switch (mode) {
+    case DS_PLAIN:
+      hipLaunchKernelGGL((k_dslash_rb<R, DS_PLAIN, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
+                         (R)diag, partials, nrhs, mq);
+      break;
+    case DS_RESID:
+      hipLaunchKernelGGL((k_dslash_rb<R, DS_RESID, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
+                         (R)diag, partials, nrhs, mq);
+      break;
+    case DS_MR:
+      hipLaunchKernelGGL((k_dslash_rb<R, DS_MR, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
+                         (R)diag, partials, nrhs, mq);
+      break;
+    case DS_MRQ:
+      if constexpr (std::is_same<TI, TO>::value && sizeof(R) == 4)
+        hipLaunchKernelGGL((k_dslash_rb<R, DS_MRQ, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
+                           (R)diag, partials, nrhs, mq);
+      else
+        return hipErrorInvalidValue;
+      break;
+  }
+  return hipGetLastError();
+}
+
 template <typename R, int NL, typename S, typename TI, typename TO>
 static hipError_t launch(const Geom &g, const S *U, const TI *in, TO *out, const TO *b, double diag, int nrhs,
                          DslashMode mode, double *partials, hipStream_t st, MrqArgs<TO> mq) {
   if (nrhs > 1) {
-    constexpr int K = mrhs_k<R, TI>();
-    dim3 grid(dslash_blocks(g), (nrhs + K - 1) / K);
-    switch (mode) {
-      case DS_PLAIN:
-        hipLaunchKernelGGL((k_dslash_rb<R, DS_PLAIN, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                           (R)diag, partials, nrhs, mq);
-        break;
-      case DS_RESID:
-        hipLaunchKernelGGL((k_dslash_rb<R, DS_RESID, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                           (R)diag, partials, nrhs, mq);
-        break;
-      case DS_MR:
-        hipLaunchKernelGGL((k_dslash_rb<R, DS_MR, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                           (R)diag, partials, nrhs, mq);
-        break;
-      case DS_MRQ:
-        if constexpr (std::is_same<TI, TO>::value && sizeof(R) == 4)
-          hipLaunchKernelGGL((k_dslash_rb<R, DS_MRQ, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                             (R)diag, partials, nrhs, mq);
-        else
-          return hipErrorInvalidValue;
-        break;
-    }
-    return hipGetLastError();
+    if constexpr (!(sizeof(R) == 8 && std::is_same<TI, double2>::value))
+      if (take_three<R, TI>(nrhs))
+        return launch_rb<R, NL, S, 3>(g, U, in, out, b, diag, nrhs, mode, partials, st, mq);
+    return launch_rb<R, NL, S, 2>(g, U, in, out, b, diag, nrhs, mode, partials, st, mq);
   }
   dim3 grid(dslash_blocks(g), nrhs);
   switch (mode) {
