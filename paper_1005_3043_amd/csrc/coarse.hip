@@ -335,8 +335,10 @@ __global__ __launch_bounds__(512) void k_coarse(Geom g, int n, const S *__restri
 // Bound by the latency of an exchange (store, acknowledge, announce, poll,
 // load).  16^3 x 32, n = 40, FP16 storage, 512 sites, 45 iterations: 835 us a
 // launch with p and r exchanged as well and the sums acknowledged after the
-// vectors, 570 us (6.3 us per phase) now.  8^4, n = 16, FP64, 16 sites: a
-// solve of 47.2 ms as chunks of launches takes 24.2 ms.
+// vectors, 570 us with that gone, and about 460 us (5 us per phase) with the
+// rows' sums on the first wavefront and the reads of apply in flight together.
+// 8^4, n = 16, FP64, 16 sites: a solve of 47 ms as chunks of launches takes
+// 24.4 ms.
 constexpr int CGP_PMAX = 16;          // most operator entries per thread kept in registers
 
 // Data exchanged between workgroups inside the launch is read and written as
@@ -364,23 +366,27 @@ __device__ __forceinline__ void cst(double2 *p, double2 v) {
 // The exchange at the end of a phase: everybody's two partial sums, and with
 // them the knowledge that everybody's vector entries are there.
 //
-// Few workgroups (CGP_DIRECT at most): a workgroup announces itself with its
-// sums, each as two 64-bit words of 32 value bits under a 32-bit tag (the
-// launch's epoch plus the phase number), and everybody polls all the words
-// until they carry the phase's tag: barrier and reduction in one round trip.
-// The words alternate between two sets: a workgroup writes a set again two
-// phases later, which it only reaches after everybody has announced the phase
-// between, that is, has read the set.  With 16 workgroups 4.6 us per phase; with
-// 512 every poll of everybody moves 8 MB and a solve takes 1.3 times as long
-// as with the counters below.
+// Few workgroups (CGP_DIRECT at most): every 64-bit word that travels, of the
+// sums and of the vector entries, carries 32 value bits under a 32-bit tag (the
+// launch's epoch plus the phase number), and whoever needs it polls it until it
+// carries the phase's tag: one way from the store to the reader, with no
+// acknowledgement, no arrival and no load after it.  A sum or an entry of z or
+// w is written again two phases later, which its writer only reaches after
+// everybody has announced the phase between, that is, has read it (the sums
+// alternate between two sets, z and w between phases).  8^4, 16 workgroups:
+// 3.4 us per phase with the entries acknowledged, announced and then loaded,
+// 3.0 us now, of which 2.1 are the exchange (one agent-scope load takes 0.7).
+// With every thread polling, also those without an entry, 4.6 us; with 512
+// workgroups every poll of everybody's sums moves 8 MB and a solve takes 1.3
+// times as long as with the counters below.
 //
-// More: the sums are stored, then an arrival is counted, and the first
+// More: the sums and entries are stored, then an arrival is counted, and the first
 // wavefront polls the counters; the sums are loaded after that, beside the
 // vector entries of the next phase.  Arrivals are spread over CGP_NC counters
 // on separate 256-byte lines, so that no address takes every workgroup's
 // atomic.
 //
-// Why relaxed atomics order it: every value another workgroup reads was stored
+// Why relaxed atomics order that form: every value another workgroup reads was stored
 // with an agent-scope atomic store (written through to the agent's coherence
 // point) and is read with an agent-scope atomic load (which bypasses the XCD's
 // L2 and reads at that point).  s_waitcnt(0) holds each thread until its stores
@@ -390,125 +396,175 @@ __device__ __forceinline__ void cst(double2 *p, double2 v) {
 // workgroup barrier order them after the polls).  A release / acquire pair
 // would give the same order with an L2 write-back and invalidate per phase;
 // with no exchanged data ever held in L2 they are not needed.
-constexpr uint32_t CGP_DIRECT = 128;
 constexpr int CGP_NC = 64;  // arrival counters: 8, 16, 32 and 64 measured alike
 
 // The set of a phase: tagged words first, bare sums (which could look like a
 // tag) behind them.
-__device__ __forceinline__ size_t cgp_set(uint32_t nblk, uint32_t tag) {
-  return nblk <= CGP_DIRECT ? (size_t)(tag & 1u) * 4 * nblk : 8 * CGP_DIRECT + (size_t)(tag & 1u) * 2 * nblk;
+template <bool DIRECT> __device__ __forceinline__ size_t cgp_set(uint32_t nblk, uint32_t tag) {
+  return DIRECT ? (size_t)(tag & 1u) * 4 * nblk : 8 * CGP_DIRECT + (size_t)(tag & 1u) * 2 * nblk;
 }
 
+template <bool DIRECT>
 __device__ __forceinline__ void cgp_announce(double (&v)[2], unsigned long long *words, unsigned *bar, uint32_t nblk,
-                                             uint32_t tag, double *lds) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-#pragma unroll
-  for (int q = 0; q < 2; ++q) v[q] = wave_sum(v[q]);
-  if (lane == 0) {
-    lds[w * 2] = v[0];
-    lds[w * 2 + 1] = v[1];
-  }
-  const bool direct = nblk <= CGP_DIRECT;
-  unsigned long long *set = words + cgp_set(nblk, tag);
-  if (direct) __builtin_amdgcn_s_waitcnt(0);  // this thread's stores acknowledged
-  __syncthreads();
+                                             uint32_t tag) {
+  // the rows of a site (n <= 64), so its sums and entries, are the first
+  // wavefront's; adding the other wavefronts' zeros would change nothing
+  if (threadIdx.x >= 64) return;
+  const double s0 = wave_sum(v[0]), s1 = wave_sum(v[1]);
+  unsigned long long *set = words + cgp_set<DIRECT>(nblk, tag);
   const int q = (threadIdx.x >> 1) & 1;  // direct: thread 2 q + h announces half h of sum q
-  unsigned long long u = 0;
-  if (threadIdx.x < 4) {
-    double a = 0.0;
-    for (int j = 0; j < nw; ++j) a += lds[j * 2 + q];
-    u = __builtin_bit_cast(unsigned long long, a);
-    if (direct) {
-      const unsigned long long half = (threadIdx.x & 1) ? u >> 32 : u & 0xffffffffull;
-      xst(set + (size_t)threadIdx.x * nblk + blockIdx.x, (unsigned long long)tag << 32 | half);
-    } else if ((threadIdx.x & 1) == 0) {
-      xst(set + (size_t)q * nblk + blockIdx.x, u);
-    }
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, q ? s1 : s0);
+  if constexpr (DIRECT) {
+    const unsigned long long half = (threadIdx.x & 1) ? u >> 32 : u & 0xffffffffull;
+    if (threadIdx.x < 4) xst(set + (size_t)threadIdx.x * nblk + blockIdx.x, (unsigned long long)tag << 32 | half);
+  } else {
+    if (threadIdx.x < 4 && (threadIdx.x & 1) == 0) xst(set + (size_t)q * nblk + blockIdx.x, u);
+    __builtin_amdgcn_s_waitcnt(0);  // the vector entries and the sums, acknowledged together
+    __builtin_amdgcn_wave_barrier();
+    if (threadIdx.x == 0)
+      __hip_atomic_fetch_add(bar + (blockIdx.x % CGP_NC) * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (direct) return;
-  __builtin_amdgcn_s_waitcnt(0);  // the vector entries and the sums, acknowledged together
-  __syncthreads();
-  if (threadIdx.x == 0)
-    __hip_atomic_fetch_add(bar + (blockIdx.x % CGP_NC) * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A vector entry as tagged words (a site's, word by word: the words of a
+// wavefront's entries are contiguous), and the wait for up to two of them.
+template <typename C> constexpr int CGP_CW = sizeof(C) / 4;
+template <typename C>
+__device__ __forceinline__ void cgp_put(unsigned long long *w, C v, uint32_t tag) {
+  struct W {
+    uint32_t u[CGP_CW<C>];
+  };
+  const W x = __builtin_bit_cast(W, v);
+#pragma unroll
+  for (int j = 0; j < CGP_CW<C>; ++j) xst(w + j, (unsigned long long)tag << 32 | x.u[j]);
+}
+template <typename C>
+__device__ __forceinline__ bool cgp_take(const unsigned long long *w0, const unsigned long long *w1, bool two, C &x0,
+                                         C &x1, uint32_t tag, unsigned spin_max) {
+  constexpr int NW = CGP_CW<C>;
+  struct W {
+    uint32_t u[NW];
+  } a, b;
+  for (unsigned spins = 0;;) {
+    unsigned long long u[2 * NW];
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      u[j] = xld(w0 + j);
+      u[NW + j] = two ? xld(w1 + j) : u[j];
+    }
+    bool all = true;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      all = all && (uint32_t)(u[j] >> 32) == tag && (uint32_t)(u[NW + j] >> 32) == tag;
+      a.u[j] = (uint32_t)u[j];
+      b.u[j] = (uint32_t)u[NW + j];
+    }
+    if (all) break;
+    if (++spins > spin_max) return false;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  x0 = __builtin_bit_cast(C, a);
+  x1 = __builtin_bit_cast(C, b);
+  return true;
 }
 
 // Waits for every workgroup's announcement of `tag` (the phase-th of the
-// launch), calls pre() (which issues the next phase's loads) and sums the
-// values in block_allsum3's order, so that each sum equals the chunked path's
-// of the same array.  False when a wait gave up.
-template <typename F>
+// launch), calls pre() (which fetches the next phase's entries; false when its
+// wait gave up) and sums the values in block_allsum3's order, so that each sum
+// equals the chunked path's of the same array.  False, for the whole
+// workgroup, when a wait gave up.  Tagged words: the last
+// wavefront, which holds no entries of small sites, polls the sums.  *bad: zero until a wait gives up.
+template <bool DIRECT, typename F>
 __device__ __forceinline__ bool cgp_gather(const unsigned long long *words, unsigned *bar, uint32_t nblk,
-                                           uint32_t tag, uint32_t phase, double (&out)[2], double *lds, int *lds_ok,
+                                           uint32_t tag, uint32_t phase, double (&out)[2], double *lds, int *bad,
                                            int *fail, unsigned spin_max, F &&pre) {
-  const unsigned long long *set = words + cgp_set(nblk, tag);
+  const unsigned long long *set = words + cgp_set<DIRECT>(nblk, tag);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  double v[2] = {0.0, 0.0};
-  int ok = 1;
   unsigned spins = 0;
-  if (nblk <= CGP_DIRECT) {
-    for (uint32_t i = threadIdx.x; i < nblk && ok; i += blockDim.x) {
-      unsigned long long u[4];
-      for (;;) {
-        bool all = true;
+  if constexpr (DIRECT) {
+    static_assert(CGP_DIRECT <= 128, "two announcements per lane");
+    int ok = 1;
+    if (w == nw - 1) {
+      double v[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) u[q] = xld(set + (size_t)q * nblk + i);
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t i = lane + 64 * j;
+        if (i >= nblk) continue;
+        for (;;) {
+          unsigned long long u[4];
+          bool all = true;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) all = all && (uint32_t)(u[q] >> 32) == tag;
-        if (all) break;
-        if (++spins > spin_max) {
-          ok = 0;
-          break;
+          for (int q = 0; q < 4; ++q) u[q] = xld(set + (size_t)q * nblk + i);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) all = all && (uint32_t)(u[q] >> 32) == tag;
+          v[j][0] = __builtin_bit_cast(double, (u[0] & 0xffffffffull) | (u[1] << 32));
+          v[j][1] = __builtin_bit_cast(double, (u[2] & 0xffffffffull) | (u[3] << 32));
+          if (all) break;
+          if (++spins > spin_max) {
+            ok = 0;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
         }
-        __builtin_amdgcn_s_sleep(1);
       }
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        v[q] += __builtin_bit_cast(double, (u[2 * q] & 0xffffffffull) | (u[2 * q + 1] << 32));
+      double t0 = wave_sum(v[0][0]), t1 = wave_sum(v[0][1]);
+      if (nblk > 64) {
+        t0 += wave_sum(v[1][0]);
+        t1 += wave_sum(v[1][1]);
+      }
+      if (lane == 0) {
+        lds[0] = t0;
+        lds[1] = t1;
+      }
     }
+    if (!pre()) ok = 0;
+    if (!ok) {
+      *bad = 1;
+      __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    __syncthreads();
+    out[0] = lds[0];
+    out[1] = lds[1];
+    return *bad == 0;
   } else {
     if (w == 0) {
       const unsigned target = phase * nblk;
       for (;;) {
-        unsigned c = lane < CGP_NC ? __hip_atomic_load(bar + lane * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        unsigned c = __hip_atomic_load(bar + lane * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         c = wave_sum(c);
         if (c >= target) break;
         if (++spins > spin_max) {
-          ok = 0;
+          if (lane == 0) {
+            *bad = 1;
+            __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          }
           break;
         }
         __builtin_amdgcn_s_sleep(1);
       }
-      if (lane == 0) lds_ok[8] = ok;
     }
     __syncthreads();
-    ok = lds_ok[8];
-    if (ok) {
-      pre();
-      for (uint32_t i = threadIdx.x; i < nblk; i += blockDim.x) {
-        v[0] += __builtin_bit_cast(double, xld(set + i));
-        v[1] += __builtin_bit_cast(double, xld(set + nblk + i));
-      }
+    if (*bad != 0) return false;
+    pre();
+    double v[2] = {0.0, 0.0};
+    for (uint32_t i = threadIdx.x; i < nblk; i += blockDim.x) {
+      v[0] += __builtin_bit_cast(double, xld(set + i));
+      v[1] += __builtin_bit_cast(double, xld(set + nblk + i));
     }
-  }
 #pragma unroll
-  for (int q = 0; q < 2; ++q) v[q] = wave_sum(v[q]);
-  ok = __all(ok);
-  if (lane == 0) {
-    lds[w * 2] = v[0];
-    lds[w * 2 + 1] = v[1];
-    lds_ok[w] = ok;
-    if (!ok) __hip_atomic_store(fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int q = 0; q < 2; ++q) v[q] = wave_sum(v[q]);
+    if (lane == 0) {
+      lds[w * 2] = v[0];
+      lds[w * 2 + 1] = v[1];
+    }
+    __syncthreads();
+    out[0] = out[1] = 0.0;
+    for (int k = 0; k < nw; ++k) {
+      out[0] += lds[k * 2];
+      out[1] += lds[k * 2 + 1];
+    }
+    return true;
   }
-  __syncthreads();
-  int good = 1;
-  for (int k = 0; k < nw; ++k) good &= lds_ok[k];
-  if (nblk <= CGP_DIRECT && good) pre();
-  out[0] = out[1] = 0.0;
-  for (int k = 0; k < nw; ++k) {
-    out[0] += lds[k * 2];
-    out[1] += lds[k * 2 + 1];
-  }
-  return good != 0;
 }
 
 // The operator entries a thread holds in registers for the whole solve, where
@@ -528,16 +584,18 @@ __device__ __forceinline__ typename OpVec<S, RW>::V kept_packed(const typename O
   }
 }
 
-template <typename R, typename S, int RW, int PM>
-__global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cgnr_persistent(Geom g, int n, const S *__restrict__ L,
+// DIRECT: at most CGP_DIRECT workgroups, one per CU, so two wavefronts' worth
+// of registers per SIMD lane.
+template <typename R, typename S, int RW, int PM, bool DIRECT>
+__global__ __launch_bounds__(512, DIRECT || (sizeof(S) == 16 && PM == 16) ? 2 : 4) void k_cgnr_persistent(Geom g, int n, const S *__restrict__ L,
                                                             CgPersist<c_t<R>> a) {
   using C = c_t<R>;
   using VT = typename OpVec<S, RW>::V;
   __shared__ C vin[9 * COARSE_NMAX], ploc[9 * COARSE_NMAX], rloc[9 * COARSE_NMAX];
   __shared__ C red[512 * RW];
   __shared__ C red2[CO_PARTS * COARSE_NMAX];
-  __shared__ double asum[16], gsum[2][16];
-  __shared__ int gok[2][9];
+  __shared__ double gsum[2][16];
+  __shared__ int bad;
   __shared__ uint32_t nbs[9];
   const uint32_t s = blockIdx.x, nblk = gridDim.x;
   const int tid = threadIdx.x;
@@ -551,8 +609,10 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cg
   for (int q = 0; q < PM; ++q) {
     const int p = grp + q * G;
     lv[q] = Ls[(size_t)((on && p < nP) ? p : 0) * n / RW];
+    if (!(on && p < nP)) lv[q] = VT{};
   }
   if (tid < 9) nbs[tid] = slot_site(g, s, tid);
+  if (tid == 0) bad = 0;
   __syncthreads();
   // where this thread's staged entries tid and tid + blockDim come from
   const int i0 = tid, i1 = tid + (int)blockDim.x;  // 9 n <= 2 blockDim
@@ -574,13 +634,13 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cg
 #pragma unroll
     for (int q = 0; q < PM; ++q) {
       const int p = grp + q * G;
-      if (on && p < nP) {
-        const C x = vin[p];
-        C o[RW];
-        OpVec<S, RW>::get(kept_packed<S, RW>(lv[q]), o);
+      // spare entries of the operator are zero: no branch, so that the reads of
+      // all entries are in flight together
+      const C x = vin[p < nP ? p : nP - 1];
+      C o[RW];
+      OpVec<S, RW>::get(kept_packed<S, RW>(lv[q]), o);
 #pragma unroll
-        for (int t = 0; t < RW; ++t) acc[t] = cfma(o[t], x, acc[t]);
-      }
+      for (int t = 0; t < RW; ++t) acc[t] = cfma(o[t], x, acc[t]);
     }
 #pragma unroll
     for (int t = 0; t < RW; ++t) red[tid * RW + t] = acc[t];
@@ -617,7 +677,26 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cg
     }
     if (tid < n) sq = (double)b0.x * b0.x + (double)b0.y * b0.y;
   }
-  C e = mk<C>(0, 0), x0, x1;
+  C e = mk<C>(0, 0), x0 = e, x1 = e;
+  // the entries of z (which 0) and w (1): tagged words, or the arrays themselves
+  constexpr int CW = CGP_CW<C>;
+  unsigned long long *ew = a.words + CGP_WORDS;
+  const size_t ews = (size_t)CGP_DIRECT * COARSE_NMAX * 4;
+  const uint32_t p0 = h0 ? o0 : s * n, p1 = h1 ? o1 : p0;
+  auto put = [&](C *arr, int which, C v, uint32_t ph) {
+    if constexpr (DIRECT) cgp_put(ew + which * ews + (size_t)own * CW, v, a.epoch + ph);
+    else cst(arr + own, v);
+  };
+  auto take = [&](const C *arr, int which, uint32_t ph) -> bool {
+    if constexpr (DIRECT) {
+      return !h0 || cgp_take(ew + which * ews + (size_t)p0 * CW, ew + which * ews + (size_t)p1 * CW, h1, x0, x1,
+                             a.epoch + ph, a.spin);
+    } else {
+      x0 = cld(arr + p0);
+      x1 = h1 ? cld(arr + p1) : x0;
+      return true;
+    }
+  };
   double sums[2], gam = 0.0, tol2b2 = 0.0;  // gam: ||z_k||^2
   int k = 0, final_it = 0;
   unsigned phase = 0;
@@ -628,15 +707,14 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cg
       double v[2] = {0.0, sq};
       if (tid < n) {
         if (tid >= half) zv = mk<C>(-zv.x, -zv.y);
-        cst(a.z + own, zv);
+        put(a.z, 0, zv, phase + 1);
         v[0] = (double)zv.x * zv.x + (double)zv.y * zv.y;
       }
       ++phase;
-      cgp_announce(v, a.words, bar, nblk, a.epoch + phase, asum);
+      cgp_announce<DIRECT>(v, a.words, bar, nblk, a.epoch + phase);
     }
-    if (!cgp_gather(a.words, bar, nblk, a.epoch + phase, phase, sums, gsum[0], gok[0], a.fail, a.spin, [&]() {
-          x0 = cld(a.z + o0);
-          x1 = h1 ? cld(a.z + o1) : x0;
+    if (!cgp_gather<DIRECT>(a.words, bar, nblk, a.epoch + phase, phase, sums, gsum[0], &bad, a.fail, a.spin, [&]() {
+          return take(a.z, 0, phase);
         }))
       break;
     R beta = 0;
@@ -662,15 +740,14 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 && PM == 16 ? 2 : 4) void k_cg
       const C wv = apply();
       double v[2] = {0.0, 0.0};
       if (tid < n) {
-        cst(a.w + own, wv);
+        put(a.w, 1, wv, phase + 1);
         v[0] = (double)wv.x * wv.x + (double)wv.y * wv.y;
       }
       ++phase;
-      cgp_announce(v, a.words, bar, nblk, a.epoch + phase, asum);
+      cgp_announce<DIRECT>(v, a.words, bar, nblk, a.epoch + phase);
     }
-    if (!cgp_gather(a.words, bar, nblk, a.epoch + phase, phase, sums, gsum[1], gok[1], a.fail, a.spin, [&]() {
-          x0 = cld(a.w + o0);
-          x1 = h1 ? cld(a.w + o1) : x0;
+    if (!cgp_gather<DIRECT>(a.words, bar, nblk, a.epoch + phase, phase, sums, gsum[1], &bad, a.fail, a.spin, [&]() {
+          return take(a.w, 1, phase);
         }))
       break;
     if (!(sums[0] > 0.0)) {
@@ -716,19 +793,18 @@ hipError_t cgnr_persistent(const Geom &g, int n, const S *L, const CgPersist<c_t
   void *kargs[] = {&gg, &nn, &LL, &args};
   // entries per thread decide the register array: 8 where they fit
   const bool p8 = pm <= 8;
-  const void *fn;
-  if constexpr (sizeof(S) == 4) {
-    if (RW == 4 && !p8) return hipErrorInvalidValue;  // 16 four-row entries would spill
-    if (RW == 4) fn = reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 4, 8>);
-    else fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 8>)
-                 : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 16>);
-  } else if constexpr (sizeof(S) == 8) {
-    fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 8>)
-            : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 2, 16>);
-  } else {
-    fn = p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 1, 8>)
-            : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 1, 16>);
-  }
+  auto pick = [&](auto direct) -> const void * {
+    constexpr bool D = decltype(direct)::value;
+    if constexpr (sizeof(S) == 4) {
+      if (RW == 4 && !p8) return nullptr;  // 16 four-row entries would spill
+      if (RW == 4) return reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, 4, 8, D>);
+    }
+    constexpr int W = sizeof(S) == 16 ? 1 : 2;
+    return p8 ? reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, W, 8, D>)
+              : reinterpret_cast<const void *>(&k_cgnr_persistent<R, S, W, 16, D>);
+  };
+  const void *fn = g.V <= CGP_DIRECT ? pick(std::true_type()) : pick(std::false_type());
+  if (fn == nullptr) return hipErrorInvalidValue;
   return hipLaunchCooperativeKernel(fn, dim3(g.V), dim3(th), kargs, 0, st);
 }
 template hipError_t cgnr_persistent<float, chalf>(const Geom &, int, const chalf *, const CgPersist<float2> &,

@@ -301,11 +301,47 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblk) {
 }
 
 // ---------------------------------------------------------------- reductions
-// Wavefront (64 lanes) sum via cross-lane shuffles.
+// v from lane ^ OFF of the wavefront, where the values repeat every 2 OFF lanes
+// (as they do when a sum over lanes takes the offsets from 32 down): lane swaps
+// of the vector unit and rotations within rows of 16, a few cycles a step, where
+// a shuffle goes through LDS (about 120).  All 64 lanes take part.
+template <int OFF> __device__ __forceinline__ void lane_xor_pair(uint32_t &a, uint32_t &b) {
+  if constexpr (OFF == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    a = r[0];
+    b = r[1];
+  } else if constexpr (OFF == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    b = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x120 | OFF, 0xf, 0xf, true);  // row_ror:OFF
+  }
+}
+template <int OFF, typename T> __device__ __forceinline__ T lane_xor_sum(T v) {
+  if constexpr (sizeof(T) == 4) {
+    uint32_t a = __builtin_bit_cast(uint32_t, v), b;
+    lane_xor_pair<OFF>(a, b);
+    return __builtin_bit_cast(T, a) + __builtin_bit_cast(T, b);
+  } else {
+    const unsigned long long x = __builtin_bit_cast(unsigned long long, v);
+    uint32_t al = (uint32_t)x, ah = (uint32_t)(x >> 32), bl, bh;
+    lane_xor_pair<OFF>(al, bl);
+    lane_xor_pair<OFF>(ah, bh);
+    return __builtin_bit_cast(T, (unsigned long long)ah << 32 | al) +
+           __builtin_bit_cast(T, (unsigned long long)bh << 32 | bl);
+  }
+}
+// Wavefront (64 lanes) sum, in every lane; the tree of pairs is that of
+// offsets 32, 16, 8, 4, 2, 1.
 template <typename T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two words");
+  v = lane_xor_sum<32>(v);
+  v = lane_xor_sum<16>(v);
+  v = lane_xor_sum<8>(v);
+  v = lane_xor_sum<4>(v);
+  v = lane_xor_sum<2>(v);
+  return lane_xor_sum<1>(v);
 }
 
 // Block sum of NV doubles: result valid in thread 0.  blockDim.x <= 1024,

@@ -131,7 +131,8 @@ struct CgFuse {
 };
 // Whole coarsest-level CGNR of one right-hand side in one cooperative launch,
 // from b alone (e = 0): the chunked fused iteration's arithmetic with a grid
-// exchange between its phases.  words: CGP_WORDS per workgroup, and bar:
+// exchange between its phases.  words: CGP_ALL_WORDS (CGP_WORDS for sums, two
+// vectors' tagged entries of small grids behind them), and bar:
 // CGP_BAR_WORDS arrival counters, both zeroed once; epoch: advanced by more
 // than the launch's exchanges (2 maxit + 2) from one launch to the next;
 // launch: number of the launch on these buffers; it (two ints: iterations) and
@@ -139,7 +140,9 @@ struct CgFuse {
 // Returns an error without launching when the shape does not suit the
 // kernel, and the cooperative launch's error when the grid cannot be
 // co-resident; the caller then takes the chunked path.
-constexpr int CGP_WORDS = 8;
+constexpr int CGP_WORDS = 8192;       // 4 words per site and set, up to 1024 sites
+constexpr uint32_t CGP_DIRECT = 128;  // sites up to which the entries are tagged
+constexpr int CGP_ALL_WORDS = CGP_WORDS + 2 * (int)CGP_DIRECT * COARSE_NMAX * 4;
 constexpr int CGP_BAR_WORDS = 2 * 64 * 64;  // two sets of 64 counters, one per 256-byte line
 template <typename C> struct CgPersist {
   const C *b = nullptr;

@@ -842,7 +842,7 @@ int cgnr_whole(mg_ctx *c, int l, const vec_t<P> *b, vec_t<P> *e, hipStream_t st,
   if (c->cgp_off[l][pc]) return MG_OK;
   Level &L = c->lev[l];
   Work<R> &w = work<R>(c);
-  MG_TRY(c->cgp_words.alloc((size_t)CGP_WORDS * CG_FUSE_MAXV));
+  MG_TRY(c->cgp_words.alloc(CGP_ALL_WORDS));
   MG_TRY(c->cgp_bar.alloc(CGP_BAR_WORDS));
   CgPersist<c_t<R>> a;
   a.b = b;
