@@ -347,8 +347,110 @@ template <typename R, typename TI> bool take_three(int nrhs) {
   return !(sizeof(R) == 8 && std::is_same<TI, double2>::value) && (nrhs + 2) / 3 * 3 <= (nrhs + 1) / 2 * 2;
 }
 
+// Latency form: the eight hops of a 64-site tile run on eight wavefronts at
+// once (one round trip of loads instead of eight) and leave their
+// contributions in LDS, where four wavefronts add three components each in
+// the order of the other kernels (bit-identical results); the first wavefront
+// finishes the sites.  Sums: one partial per tile.  Bound by latency: of its
+// 4.7 us (8^4, FP64; 10.9 with the hops in turn) about 2 are the loads.
+template <typename R, int MODE, int NL, typename S, typename TI, typename TO>
+__global__ __launch_bounds__(512, 2) void k_dslash_split(Geom g, const S *__restrict__ U, const TI *__restrict__ in,
+                                                         TO *__restrict__ out, const TO *__restrict__ b, R diag,
+                                                         double *__restrict__ partials, MrqArgs<TO> mq) {
+  using C = c_t<R>;
+  __shared__ C hop[8][12][64];
+  const int lane = threadIdx.x & 63, h = threadIdx.x >> 6;
+  in += (size_t)blockIdx.y * site_slots<TI>() * g.Vpad;
+  const size_t off = (size_t)blockIdx.y * site_slots<TO>() * g.Vpad;
+  out += off;
+  const uint32_t s0 = blockIdx.x * 64 + lane;
+  const bool live = s0 < g.V;
+  const uint32_t s = live ? s0 : g.V - 1;
+  C ctr[12];
+  if (h == 0) load_site(ctr, in, s);
+  {
+    const Coords k = decode(g, s);
+    const int mu = h >> 1;
+    const bool fwd = (h & 1) == 0;
+    const int o = mu == 0 ? k.o[0] : mu == 1 ? k.o[1] : mu == 2 ? k.o[2] : k.o[3];
+    const int c = mu == 0 ? k.c[0] : mu == 1 ? k.c[1] : mu == 2 ? k.c[2] : k.c[3];
+    const uint32_t sn = fwd ? nbr_fwd(g, s, o, c, mu) : nbr_bwd(g, s, o, c, mu);
+    R eta = 1;
+    if (mu == 3 && g.antiperiodic && (fwd ? o == g.b[3] - 1 && c == g.C[3] - 1 : o == 0 && c == 0)) eta = -1;
+    C p[12], u[9], acc[12];
+    load_site(p, in, sn);
+    load_link_t<NL>(u, U, mu, fwd ? s : sn);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) acc[i] = mk<C>(0, 0);
+    if (fwd) hop_dispatch<true>(mu, acc, p, u, eta);
+    else hop_dispatch<false>(mu, acc, p, u, eta);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) hop[h][i][lane] = acc[i];
+  }
+  __syncthreads();
+  if (h < 4) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      C t = hop[0][3 * h + i][lane];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) t = cadd(t, hop[q][3 * h + i][lane]);
+      hop[0][3 * h + i][lane] = t;  // read by this lane only
+    }
+  }
+  __syncthreads();
+  if (h != 0) return;
+  C res[12];
+#pragma unroll
+  for (int i = 0; i < 12; ++i) {
+    const C a = hop[0][i][lane];
+    res[i].x = fma(diag, ctr[i].x, (R)-0.5 * a.x);
+    res[i].y = fma(diag, ctr[i].y, (R)-0.5 * a.y);
+  }
+  double red[3] = {0.0, 0.0, 0.0};
+  if (live) {
+    if constexpr (MODE == DS_RESID) {
+      C bb[12];
+      load_site_nt(bb, b + off, s);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) res[i] = csub(bb[i], res[i]);
+    }
+    if constexpr (MODE == DS_MRQ) mrq_site(res, ctr, mq.rprev + off, out, mq.rout + off, s, mq.alpha[blockIdx.y]);
+    else store_site(out, s, res);
+    if constexpr (MODE == DS_MR || MODE == DS_MRQ) {
+#pragma unroll
+      for (int i = 0; i < 12; ++i) {
+        red[0] += (double)res[i].x * ctr[i].x + (double)res[i].y * ctr[i].y;
+        red[1] += (double)res[i].x * ctr[i].y - (double)res[i].y * ctr[i].x;
+        red[2] += (double)res[i].x * res[i].x + (double)res[i].y * res[i].y;
+      }
+    }
+  }
+  if constexpr (MODE == DS_MR || MODE == DS_MRQ) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) red[q] = wave_sum(red[q]);
+    if (lane == 0) {
+      double *p = partials + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 3;
+      p[0] = red[0];
+      p[1] = red[1];
+      p[2] = red[2];
+    }
+  }
+}
+
+// Tiles (all right-hand sides together) up to which the latency form runs:
+// beyond, its traffic and the single finishing wavefront cost more than the
+// round trips.  This form / the others, in us: 64 tiles FP64 4.7 / 10.9, FP32
+// 4.4 / 9.7, FP16 class 4.2 / 9.2; 324 tiles 9.0 / 12.7, 5.8 / 9.8, 5.1 / 9.3;
+// 512 tiles 11.2 / 11.9, 6.3 / 10.0, 5.3 / 9.4; 1024 tiles 21 / 15, 11.3 /
+// 10.6, 8.9 / 9.4.  Several right-hand sides: 64 x 12 tiles 14 / 19, 8.3 / 22,
+// 7.8 / 19; 128 x 12 tiles FP64 26 / 22.  One line for all types, since the
+// number of partial sums follows it.
+static bool take_split(const Geom &g, int nrhs) {
+  return (uint64_t)div_up(g.V, 64) * nrhs <= (nrhs == 1 ? 512u : 768u);
+}
+
 int dslash_blocks(const Geom &g) { return div_up(g.V, 256); }
-int dslash_partials(const Geom &g, int) { return dslash_blocks(g); }
+int dslash_partials(const Geom &g, int nrhs) { return take_split(g, nrhs) ? div_up(g.V, 64) : dslash_blocks(g); }
 
 template <typename R, int NL, typename S, int K, typename TI, typename TO>
 static hipError_t launch_rb(const Geom &g, const S *U, const TI *in, TO *out, const TO *b, double diag, int nrhs,
@@ -381,6 +483,31 @@ static hipError_t launch_rb(const Geom &g, const S *U, const TI *in, TO *out, co
 template <typename R, int NL, typename S, typename TI, typename TO>
 static hipError_t launch(const Geom &g, const S *U, const TI *in, TO *out, const TO *b, double diag, int nrhs,
                          DslashMode mode, double *partials, hipStream_t st, MrqArgs<TO> mq) {
+  if (take_split(g, nrhs)) {
+    dim3 grid(div_up(g.V, 64), nrhs);
+    switch (mode) {
+      case DS_PLAIN:
+        hipLaunchKernelGGL((k_dslash_split<R, DS_PLAIN, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
+                           (R)diag, partials, mq);
+        break;
+      case DS_RESID:
+        hipLaunchKernelGGL((k_dslash_split<R, DS_RESID, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
+                           (R)diag, partials, mq);
+        break;
+      case DS_MR:
+        hipLaunchKernelGGL((k_dslash_split<R, DS_MR, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
+                           (R)diag, partials, mq);
+        break;
+      case DS_MRQ:
+        if constexpr (std::is_same<TI, TO>::value && sizeof(R) == 4)
+          hipLaunchKernelGGL((k_dslash_split<R, DS_MRQ, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
+                             (R)diag, partials, mq);
+        else
+          return hipErrorInvalidValue;
+        break;
+    }
+    return hipGetLastError();
+  }
   if (nrhs > 1) {
     if constexpr (!(sizeof(R) == 8 && std::is_same<TI, double2>::value))
       if (take_three<R, TI>(nrhs))

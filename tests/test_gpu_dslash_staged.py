@@ -1,7 +1,8 @@
-"""Fine stencil with the workgroup's own sites in LDS: volumes of one block, of
-blocks and a remainder, and of whole aggregates, with right-hand sides that
-make full and ragged groups of two and of three, in each precision class,
-against the oracle.  Bounds: rounding of about 1500 operations per site in
+"""Fine stencil in its two forms, the hops of a tile on eight wavefronts (few
+tiles) and a site per thread with the workgroup's own sites in LDS: volumes of
+whole tiles and blocks, with a remainder, and of whole aggregates, with
+right-hand sides that make full and ragged groups of two and of three, in each
+precision class, against the oracle.  Bounds: rounding of about 1500 operations per site in
 FP64 and FP32, half a binary16 unit (4.9e-4) in links and spinors otherwise."""
 import numpy as np
 import pytest
@@ -14,7 +15,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("L,block", [((4, 4, 4, 4), (2, 2, 2, 2)), ((6, 4, 2, 6), (3, 2, 1, 2)),
-                                     ((8, 4, 4, 8), (4, 4, 4, 4)), ((5, 4, 8, 4), (5, 4, 4, 2))])
+                                     ((8, 4, 4, 8), (4, 4, 4, 4)), ((5, 4, 8, 4), (5, 4, 4, 2)),
+                                     ((8, 8, 8, 16), (4, 4, 4, 4)), ((11, 13, 16, 15), (11, 1, 2, 3)),
+                                     ((16, 16, 16, 9), (4, 4, 4, 3))])
 def test_groups(cuda, L, block):
     import paper_1005_3043_amd as mgwd
     U, starts = W.gauge_field(L, 0.4, 6), W.setup_starts(L, 2, 6)
