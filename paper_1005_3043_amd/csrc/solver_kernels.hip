@@ -50,16 +50,31 @@ __device__ __forceinline__ void finish_sum(const double *__restrict__ part, int 
   block_sum<W>(tot, lds);
 }
 
-// MR: alpha = omega <q,r> / <q,q>  (stored as complex; 0 when q = 0)
-__global__ void k_fin_mr(const double *part, int np, double omega, double2 *alpha) {
+// MR: alpha = omega <q,r> / <q,q>  (stored as complex; 0 when q = 0); thread 0
+__device__ __forceinline__ double2 mr_alpha(const double *part, int np, double omega) {
   double t[3];
   finish_sum<3>(part, np, t);
-  if (threadIdx.x == 0) {
-    double2 a = make_double2(0.0, 0.0);
-    if (t[2] > 0.0) a = make_double2(omega * t[0] / t[2], omega * t[1] / t[2]);
-    alpha[blockIdx.y] = a;
-  }
+  return t[2] > 0.0 ? make_double2(omega * t[0] / t[2], omega * t[1] / t[2]) : make_double2(0.0, 0.0);
 }
+__global__ void k_fin_mr(const double *part, int np, double omega, double2 *alpha) {
+  const double2 a = mr_alpha(part, np, omega);
+  if (threadIdx.x == 0) alpha[blockIdx.y] = a;
+}
+// The step length of an update kernel: read, or where np > 0 formed here by
+// each workgroup from the partial sums (same order, same bits).
+__device__ __forceinline__ double2 mr_alpha_of(const double2 *alpha, const double *part, int np, double omega) {
+  if (np == 0) return alpha[blockIdx.y];
+  __shared__ double2 sh;
+  const double2 a = mr_alpha(part, np, omega);
+  if (threadIdx.x == 0) sh = a;
+  __syncthreads();
+  return sh;
+}
+// Partial sums up to which the update forms its step length itself: one load
+// per thread.  A launch of k_fin_mr is 4.4 us; with more partial sums the
+// update is long enough for that not to matter and would read them from every
+// workgroup.  8^4, FP64: 341 launches fewer per solve.
+constexpr int MR_OWN_ALPHA = 256;
 
 // plain sums: out[rhs*W + q]
 template <int W> __global__ void k_fin_sum(const double *part, int np, double *out) {
@@ -109,11 +124,12 @@ __global__ __launch_bounds__(256) void k_dot(const c_t<R> *a, const c_t<R> *b, s
 // MR: x = (first ? 0 : x) + alpha r;  r -= alpha q
 template <typename R>
 __global__ __launch_bounds__(256) void k_mr_update(c_t<R> *x, c_t<R> *r_out, const c_t<R> *r_in, const c_t<R> *q,
-                                                   size_t n, const double2 *alpha, int first, int upd_r) {
+                                                   size_t n, const double2 *alpha, int first, int upd_r,
+                                                   const double *part, int np, double omega) {
   using C = c_t<R>;
   const size_t off = (size_t)blockIdx.y * n;
   x += off; r_out += off; r_in += off; q += off;
-  const double2 ad = alpha[blockIdx.y];
+  const double2 ad = mr_alpha_of(alpha, part, np, omega);
   const C a = mk<C>((R)ad.x, (R)ad.y), ma = mk<C>((R)-ad.x, (R)-ad.y);
   if (upd_r) {
     GSTRIDE(i, n) {
@@ -131,11 +147,11 @@ __global__ __launch_bounds__(256) void k_mr_update(c_t<R> *x, c_t<R> *r_out, con
 // residual's scale is formed from all 12 of its components.
 __global__ __launch_bounds__(256) void k_mr_update_h(float2 *x, h16 *r_out, const h16 *r_in, const h16 *q,
                                                      uint32_t V, uint32_t Vpad, const double2 *alpha, int first,
-                                                     int upd_r) {
+                                                     int upd_r, const double *part, int np, double omega) {
   x += (size_t)blockIdx.y * 12 * Vpad;
   const size_t off = (size_t)blockIdx.y * 13 * Vpad;
   r_out += off; r_in += off; q += off;
-  const double2 ad = alpha[blockIdx.y];
+  const double2 ad = mr_alpha_of(alpha, part, np, omega);
   const float2 a = make_float2((float)ad.x, (float)ad.y), ma = make_float2((float)-ad.x, (float)-ad.y);
   GSTRIDE(i, V) {
     const uint32_t s = (uint32_t)i;
@@ -479,18 +495,20 @@ template <typename R>
 hipError_t mr_update(c_t<R> *x, c_t<R> *r_out, const c_t<R> *r_in, const c_t<R> *q, size_t n, int nrhs,
                      const double *part, int np, double omega, double2 *alpha, int first, int upd_r,
                      hipStream_t st) {
-  hipLaunchKernelGGL(k_fin_mr, dim3(1, nrhs), dim3(256), 0, st, part, np, omega, alpha);
+  const bool own = np <= MR_OWN_ALPHA;
+  if (!own) hipLaunchKernelGGL(k_fin_mr, dim3(1, nrhs), dim3(256), 0, st, part, np, omega, alpha);
   hipLaunchKernelGGL(k_mr_update<R>, dim3(sgrid(n), nrhs), dim3(256), 0, st, x, r_out, r_in, q, n, alpha, first,
-                     upd_r);
+                     upd_r, part, own ? np : 0, omega);
   return hipGetLastError();
 }
 
 hipError_t mr_update_h(float2 *x, h16 *r_out, const h16 *r_in, const h16 *q, const Geom &g, int nrhs,
                        const double *part, int np, double omega, double2 *alpha, int first, int upd_r,
                        hipStream_t st) {
-  hipLaunchKernelGGL(k_fin_mr, dim3(1, nrhs), dim3(256), 0, st, part, np, omega, alpha);
+  const bool own = np <= MR_OWN_ALPHA;
+  if (!own) hipLaunchKernelGGL(k_fin_mr, dim3(1, nrhs), dim3(256), 0, st, part, np, omega, alpha);
   hipLaunchKernelGGL(k_mr_update_h, dim3(sgrid(g.V), nrhs), dim3(256), 0, st, x, r_out, r_in, q, g.V, g.Vpad, alpha,
-                     first, upd_r);
+                     first, upd_r, part, own ? np : 0, omega);
   return hipGetLastError();
 }
 
