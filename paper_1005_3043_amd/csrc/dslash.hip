@@ -251,8 +251,9 @@ __global__ __launch_bounds__(256, dslash_waves<R>()) void k_dslash(Geom g, const
 // groups one after another over the whole lattice).  On 32^3 x 64 with 12
 // right-hand sides, 512 blocks (16 chunks, 25 MB of FP32 links each):
 // FP32 2.52 -> 2.42 ms, FP16 class 1.74 -> 1.70 ms, FP64 4.77 -> 4.69 ms
-// per launch, the MR q-recursion forms within 1 %; 128 and 2048 blocks
-// gain less or lose.
+// per launch before the LDS copy, the MR q-recursion forms within 1 %; 128 and
+// 2048 blocks gained less or lost, and with the copy 256 blocks lose 2-3 %
+// against 512 (FP32 2.31 / 2.25 ms, FP64 4.07 / 3.99).
 #ifndef MG_DSLASH_CHUNK
 #define MG_DSLASH_CHUNK 512
 #endif
