@@ -58,7 +58,7 @@ __device__ __forceinline__ size_t chunk_entry(const Geom &g, uint32_t s0, int l0
 }
 
 template <bool CANON, int MT>
-__global__ __launch_bounds__(256) void k_restrict_f64(Geom g, Geom gc, int nv, int nrhs, int per,
+__global__ __launch_bounds__(256, 2) void k_restrict_f64(Geom g, Geom gc, int nv, int nrhs, int per,
                                                       const double2 *__restrict__ P,
                                                       const double2 *__restrict__ fine, double2 *__restrict__ coarse) {
   extern __shared__ double2 sF[];  // [n][TF_VEC], then the wavefronts' sums
@@ -85,9 +85,17 @@ __global__ __launch_bounds__(256) void k_restrict_f64(Geom g, Geom gc, int nv, i
   };
 #pragma unroll
   for (int c3 = 0; c3 < 3; ++c3) load_p(c3, 0);
-  doublex4 re[MT], im[MT];
+  // Sums as short as the vector kernel's, a tree over threads of 12 products
+  // each: a matrix instruction adds four products from zero, the four k-steps
+  // of a component are added, and two chunks at a time join the total.  All
+  // 768 products of a wavefront in one accumulator rounded 7 times as much
+  // (4^4 aggregates, relative to extended precision: 1.3e-15 against 1.9e-16,
+  // 1.9e-16 this way).  The additions cost 4 % of a restriction and
+  // prolongation of 12 vectors on 24^3 x 48 (1.92 -> 1.99 ms).
+  doublex4 re[MT], im[MT], sre[MT], sim[MT];
 #pragma unroll
-  for (int m = 0; m < MT; ++m) re[m] = im[m] = doublex4{0.0, 0.0, 0.0, 0.0};
+  for (int m = 0; m < MT; ++m) re[m] = im[m] = sre[m] = sim[m] = doublex4{0.0, 0.0, 0.0, 0.0};
+  const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
   const int nch = (vb + TF_SITES - 1) / TF_SITES, tot = n * TF_TOT;
   for (int ch = 0; ch < nch; ++ch) {
     __syncthreads();  // ci is there; the previous chunk has been read
@@ -108,22 +116,43 @@ __global__ __launch_bounds__(256) void k_restrict_f64(Geom g, Geom gc, int nv, i
       }
     }
     __syncthreads();
+    if ((ch & 1) == 0) {  // a new pair of chunks
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        sre[m] += re[m];
+        sim[m] += im[m];
+        re[m] = im[m] = doublex4{0.0, 0.0, 0.0, 0.0};
+      }
+    }
 #pragma unroll
     for (int c3 = 0; c3 < 3; ++c3) {
+      const double2 *bp = sF + colc * TF_VEC + q * TF_ROW + 3 * wv + c3;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double2 b = sF[colc * TF_VEC + (4 * u + q) * TF_ROW + 3 * wv + c3];
+      for (int m = 0; m < MT; ++m) {
+        doublex4 qr, qi;
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {  // conj(P) F
-          const double2 p = a[c3][m][u];
-          re[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.x, re[m], 0, 0, 0);
-          im[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.y, im[m], 0, 0, 0);
-          re[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, b.y, re[m], 0, 0, 0);
-          im[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(-p.y, b.x, im[m], 0, 0, 0);
+        for (int u = 0; u < 4; ++u) {  // conj(P) F
+          const double2 p = a[c3][m][u], f = bp[4 * u * TF_ROW];
+          const doublex4 xx = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, f.x, zero, 0, 0, 0);
+          const doublex4 xy = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, f.y, zero, 0, 0, 0);
+          const doublex4 yy = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, f.y, zero, 0, 0, 0);
+          const doublex4 yx = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, f.x, zero, 0, 0, 0);
+          qr = u == 0 ? xx + yy : qr + (xx + yy);
+          qi = u == 0 ? xy - yx : qi + (xy - yx);
         }
+        re[m] += qr;
+        im[m] += qi;
+        // added here: the compiler would keep the products of all tiles until
+        // the chunk's end, past the registers it has
+        asm volatile("" : "+v"(re[m]), "+v"(im[m]));
       }
       if (ch + 1 < nch) load_p(c3, ch + 1);
     }
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    re[m] += sre[m];
+    im[m] += sim[m];
   }
   __syncthreads();
   // the odd wavefront of each chirality hands its sums to the even one
