@@ -22,6 +22,8 @@
 // M = n rows, N = nrhs (padded to 16) and K = 9n, where A is the site's
 // operator (loaded once for every right-hand side) and B the nine staged
 // input blocks.  Each complex product is three real 16x16x4 FP32 MFMAs.
+#include <type_traits>
+
 #include "solver.h"
 
 namespace mg {
@@ -1058,19 +1060,21 @@ __global__ __launch_bounds__(512) void k_coarse_mma(Geom g, int n, const S *__re
 // stages a slot's vectors in its own LDS and reads its operator block once, so
 // no barrier stands between the slots.  Bound by the operator's bytes: with
 // one workgroup per right-hand side (k_coarse) 12 of them on 24^3 x 48 (n =
-// 48, 860 MB) took 626 us; this takes 189, 4.8 TB/s of operator and vectors.
+// 48, 860 MB) took 626 us; this takes 193, 4.7 TB/s of operator and vectors.
 // Three wavefronts per SIMD: with two, whole workgroups of three leave a
-// quarter of the slots empty (228 us).
+// quarter of the slots empty (n = 48: 228 us against 189 before the short
+// chains).  Four row tiles do not fit that and take two (n = 64: 352 us; 400
+// with 200 bytes spilled).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int MF_WAVES = 3;
 
 template <int MT>
-__global__ __launch_bounds__(64 * MF_WAVES, 3) void k_coarse_mma_f64(Geom g, int n, const double2 *__restrict__ L,
+__global__ __launch_bounds__(64 * MF_WAVES, MT == 4 ? 2 : 3) void k_coarse_mma_f64(Geom g, int n, const double2 *__restrict__ L,
                                                                   const double2 *__restrict__ in,
                                                                   double2 *__restrict__ out, int nrhs, int per,
                                                                   int dagger, double *__restrict__ part, int pw,
                                                                   const int *__restrict__ done, CgCheck chk) {
-  extern __shared__ __align__(16) double2 bl64[];  // [MF_WAVES][4 KS][ldb], then the wavefronts' sums
+  extern __shared__ __align__(16) double2 bl64[];  // [MF_WAVES][4 KP][ldb], then the wavefronts' sums
   __shared__ double rsum[MMA_NR];
   __shared__ double pr[MT][64][3];
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1081,10 +1085,12 @@ __global__ __launch_bounds__(64 * MF_WAVES, 3) void k_coarse_mma_f64(Geom g, int
   }
   if (chk.part_r != nullptr && cg_check_all(chk, nrhs, rsum)) return;
   const uint32_t s = xcd_remap(blockIdx.x, gridDim.x);
+  constexpr int U = 4;  // k-steps per load batch
   const int half = n >> 1, KS = (n + 3) >> 2, ldb = nr | 1;
   const int q = lane >> 4, col = lane & 15, colc = col < nr ? col : 0;
-  double2 *bw = bl64 + (size_t)wv * 4 * KS * ldb;
-  int row[MT];
+  const int KP = (KS + U - 1) / U * U;  // staged k-steps, zero from n on
+  double2 *bw = bl64 + (size_t)wv * 4 * KP * ldb;
+  uint32_t row[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) row[m] = min(16 * m + col, n - 1);
   const uint32_t nb = slot_site(g, s, lane < 9 ? lane : 0);
@@ -1093,14 +1099,19 @@ __global__ __launch_bounds__(64 * MF_WAVES, 3) void k_coarse_mma_f64(Geom g, int
   doublex4 re[MT], im[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) re[m] = im[m] = doublex4{0.0, 0.0, 0.0, 0.0};
-  constexpr int U = 4;  // k-steps per load batch
   double2 a[U][MT];
+  // A batch's products (two k-steps' where there are few rows) are one chain
+  // from zero, added to the sum when done: one accumulator over a wavefront's
+  // three slots rounded 1.7 times as much as k_coarse (n = 48, relative to
+  // extended precision: 7.4e-16 against 4.3e-16; 2.4e-16 this way).  24^3 x 48,
+  // n = 48, 12 right-hand sides 186 -> 193 us, n = 64 356 -> 352.
+  const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
   for (int slot = wv; slot < 9; slot += MF_WAVES) {
     const double2 *Ls = L + ((size_t)s * 9 + slot) * n * n;
     auto load = [&](int k0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const size_t o = (size_t)min(4 * (k0 + u) + q, n - 1) * n;
+        const uint32_t o = (uint32_t)(min(4 * (k0 + u) + q, n - 1) * n);
 #pragma unroll
         for (int m = 0; m < MT; ++m) a[u][m] = Ls[o + row[m]];
       }
@@ -1118,29 +1129,40 @@ __global__ __launch_bounds__(64 * MF_WAVES, 3) void k_coarse_mma_f64(Geom g, int
         for (int u = 0; u < 4; ++u)
           bw[j * ldb + min(t0 + u, nr - 1)] = neg ? make_double2(-v[u].x, -v[u].y) : v[u];
       }
-      for (int i = n * ldb + lane; i < 4 * KS * ldb; i += 64) bw[i] = make_double2(0.0, 0.0);
+      for (int i = n * ldb + lane; i < 4 * KP * ldb; i += 64) bw[i] = make_double2(0.0, 0.0);
       __builtin_amdgcn_wave_barrier();
     }
-    for (int k0 = 0; k0 < KS; k0 += U) {
+    // NK k-steps from k0 on, and the loads of the next batch
+    auto batch = [&](auto nk, int k0) {
+      constexpr int NK = decltype(nk)::value, CH = MT > 2 ? NK : 2;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (k0 + u >= KS) break;
-        const double2 b = bw[(4 * (k0 + u) + q) * ldb + colc];
+      for (int m = 0; m < MT; ++m) {
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-          const double2 p = a[u][m];
-          re[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.x, re[m], 0, 0, 0);
-          im[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.y, im[m], 0, 0, 0);
-          re[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(-p.y, b.y, re[m], 0, 0, 0);
-          im[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, b.x, im[m], 0, 0, 0);
-        }
-        if (k0 + U + u < KS) {  // the k-step after next U takes this one's registers
-          const size_t o = (size_t)min(4 * (k0 + U + u) + q, n - 1) * n;
+        for (int h = 0; h < NK / CH; ++h) {
+          doublex4 tr = zero, ti = zero;
 #pragma unroll
-          for (int m = 0; m < MT; ++m) a[u][m] = Ls[o + row[m]];
+          for (int v = 0; v < CH; ++v) {
+            const int u = CH * h + v;
+            const double2 p = a[u][m], b = bw[(4 * (k0 + u) + q) * ldb + colc];
+            tr = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.x, tr, 0, 0, 0);
+            ti = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, b.y, ti, 0, 0, 0);
+            tr = __builtin_amdgcn_mfma_f64_16x16x4f64(-p.y, b.y, tr, 0, 0, 0);
+            ti = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, b.x, ti, 0, 0, 0);
+          }
+          if (NK == U && k0 + U < KS) {  // the next batch takes the chain's registers
+#pragma unroll
+            for (int v = 0; v < CH; ++v)
+              a[CH * h + v][m] = Ls[(uint32_t)(min(4 * (k0 + U + CH * h + v) + q, n - 1) * n) + row[m]];
+          }
+          re[m] += tr;
+          im[m] += ti;
+          asm volatile("" : "+v"(re[m]), "+v"(im[m]));  // added here, not kept for all tiles
         }
       }
-    }
+    };
+    int k0 = 0;
+    for (; k0 + 2 < KS; k0 += U) batch(std::integral_constant<int, U>(), k0);
+    if (k0 < KS) batch(std::integral_constant<int, 2>(), k0);
   }
   // sums of wavefronts 1 and 2 to wavefront 0; slot 0, the centre, was wavefront 0's first
   __syncthreads();
@@ -1199,7 +1221,7 @@ __global__ __launch_bounds__(64 * MF_WAVES, 3) void k_coarse_mma_f64(Geom g, int
 static hipError_t coarse_mma_f64(const Geom &g, int n, const double2 *L, const double2 *in, double2 *out, int nrhs,
                                  int dagger, const CoarseArgs &a, const CgCheck &c, hipStream_t st) {
   const int ng = (nrhs + MMA_NR - 1) / MMA_NR, per = (nrhs + ng - 1) / ng, mt = (n + 15) / 16;
-  size_t lds = sizeof(double2) * MF_WAVES * ((n + 3) / 4 * 4) * (per | 1);
+  size_t lds = sizeof(double2) * MF_WAVES * ((n + 15) / 16 * 16) * (per | 1);
   const size_t sums = sizeof(double2) * (MF_WAVES - 1) * mt * 4 * 64;
   if (lds < sums) lds = sums;
 #define MG_MF(M)                                                                                                    \

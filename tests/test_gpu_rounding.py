@@ -44,3 +44,29 @@ def test_restriction(cuda, L, block, nv):
         print(f"restriction {L} nv {nv} x{nrhs}: {err:.2e}")
         assert err <= 2.5e-16, nrhs
     ctx.close()
+
+
+@pytest.mark.parametrize("L,block,nv", [((8, 8, 8, 8), (4, 4, 4, 4), 8), ((16, 8, 8, 8), (4, 4, 4, 4), 24),
+                                        ((8, 8, 4, 8), (4, 4, 4, 4), 32), ((8, 8, 8, 16), (4, 4, 4, 4), 10)])
+def test_coarse_operator(cuda, L, block, nv):
+    """Several right-hand sides of the coarse stencil round no more than one at
+    a time, which the vector kernel sums (a tenth is left for the sample);
+    96 of them, so that the matrix-core kernel takes
+    them on these few sites too."""
+    ctx = _context(L, block, nv)
+    X, Y = (a.astype(LD) for a in ctx.export_coarse_op(1))
+    rng = np.random.default_rng(nv)
+    nrhs = 96
+    v = rng.standard_normal((nrhs,) + X.shape[:-1]) + 1j * rng.standard_normal((nrhs,) + X.shape[:-1])
+    ref = np.einsum("...ij,n...j->n...i", X, v.astype(LD))
+    for d in range(8):
+        mu, back = divmod(d, 2)
+        nb = np.roll(v.astype(LD), 1 if back else -1, axis=(-2, -3, -4, -5)[mu])
+        ref += np.einsum("...ij,n...j->n...i", Y[d], nb)
+    dv = torch.from_numpy(v).cuda()
+    one = np.concatenate([ctx.coarse_apply(1, dv[k:k + 1]).cpu().numpy().reshape(1, *v.shape[1:]) for k in range(12)])
+    several = ctx.coarse_apply(1, dv).cpu().numpy().reshape(v.shape)
+    ctx.close()
+    e1, en = _rel(one, ref[:12]), _rel(several, ref)
+    print(f"coarse operator n {2 * nv}: one at a time {e1:.2e}, several {en:.2e}")
+    assert en <= 1.1 * e1
