@@ -1235,6 +1235,23 @@ static hipError_t coarse_mma_f64(const Geom &g, int n, const double2 *L, const d
   return hipGetLastError();
 }
 
+// Whether several FP64 right-hand sides take the matrix cores, one workgroup
+// per site, or k_coarse, one workgroup per site and right-hand side.  The
+// former takes 20 us for a site at n = 48 (6 at n = 16) however few there are,
+// the latter 9 us (5) while its workgroups fit the device, about 1 024 of them,
+// half as many where the number of sites is not a multiple of 8 and a site's
+// operator goes to every XCD's L2.  Matrix cores / k_coarse in us, n = 48: 64
+// sites x 12 right-hand sides 23 / 18; 128 x 8 25 / 22, x 12 26 / 31; 256 x 4
+// 27 / 23, x 6 28 / 32; 81 x 6 24 / 26, x 8 25 / 33; 162 x 4 25 / 33.  n = 16:
+// 64 x 12 8.0 / 8.7, 16 x 12 7.9 / 5.4.  On many sites two or three right-hand
+// sides share the reads of the operator in k_coarse too: 2 592 sites x 2, n =
+// 64 / 48 / 40 / 16 311, 177, 143, 24 / 268, 171, 129, 41; x 3, n = 64 / 48 / 40
+// 316, 179, 144 / 333, 218, 163; 512 sites, n = 40, x 3 34 / 26, x 4 34 / 32.
+static bool take_mma_f64(const Geom &g, int n, int nrhs) {
+  const int least = g.V < 1024u ? 4 : n > 16 ? 3 : 2;
+  return nrhs >= least && (uint64_t)g.V * nrhs > ((g.V & 7u) ? 512u : 1024u);
+}
+
 // Wavefronts per workgroup of variant ks (or 8 + ks): the K range in 2 ks shares.
 static int mma_waves(int ks) { return 2 * ks; }
 static size_t mma_lds_bytes(int n, int nrhs, int ks) {
@@ -1296,12 +1313,8 @@ hipError_t coarse_apply_k(const Geom &g, int n, const S *L, const c_t<R> *in, c_
     }
   } else {
     if (a.variant > 0) return hipErrorInvalidValue;
-    // From two right-hand sides on (four below 1 024 sites, where a workgroup
-    // per site leaves most of the device idle), unless the CGNR updates are
-    // fused in.  2 / 4 / 12 right-hand sides, this way against one workgroup
-    // per right-hand side: n = 48, 2 592 sites 173 / 176 / 189 and 171 / 266 /
-    // 626 us; n = 40, 512 sites 31 / 31 / 34 and 22 / 32 / 84 us.
-    if (nrhs >= (g.V < 1024u ? 4 : 2) && !(a.fuse && a.fuse->kind) && (c.part_r == nullptr || nrhs <= MMA_NR))
+    // Not where the CGNR updates are fused in.
+    if (take_mma_f64(g, n, nrhs) && !(a.fuse && a.fuse->kind) && (c.part_r == nullptr || nrhs <= MMA_NR))
       return coarse_mma_f64(g, n, L, in, out, nrhs, dagger, a, c, st);
   }
   const dim3 grid(g.V * coarse_split(n, g.V) * nrhs);

@@ -51,12 +51,12 @@ def test_restriction(cuda, L, block, nv):
 def test_coarse_operator(cuda, L, block, nv):
     """Several right-hand sides of the coarse stencil round no more than one at
     a time, which the vector kernel sums (a tenth is left for the sample);
-    96 of them, so that the matrix-core kernel takes
-    them on these few sites too."""
+    160 of them, so that the matrix-core kernel
+    takes them on these few sites too."""
     ctx = _context(L, block, nv)
     X, Y = (a.astype(LD) for a in ctx.export_coarse_op(1))
     rng = np.random.default_rng(nv)
-    nrhs = 96
+    nrhs = 160
     v = rng.standard_normal((nrhs,) + X.shape[:-1]) + 1j * rng.standard_normal((nrhs,) + X.shape[:-1])
     ref = np.einsum("...ij,n...j->n...i", X, v.astype(LD))
     for d in range(8):
