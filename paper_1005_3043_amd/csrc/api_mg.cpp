@@ -267,14 +267,14 @@ extern "C" int mg_transfer_variant(mg_ctx_t *ctx, mg_prec_t prec, int nrhs, int 
 }
 
 namespace {
-// FP64 transfers between canonical arrays.  The finest level's go straight
-// to and from the caller's fine vectors; the coarse ones, which are small,
-// are converted.
+// FP64 transfers between canonical arrays.  On the finest level the matrix-core
+// kernels go straight to and from the caller's fine vectors; the coarse ones,
+// which are small, are converted.
 int restrict_f64(mg_ctx *c, int level, const void *fine, void *coarse, int nrhs, hipStream_t st) {
   Level &L = c->lev[level], &Lc = c->lev[level + 1];
   AsyncBuf<double2> a(st), b(st);
   HIPK(b.alloc(Lc.vsize() * nrhs));
-  if (level == 0) {
+  if (level == 0 && restrict_takes_mma_f64(L.g, nrhs)) {
     HIPK(restrict_fine_f64<true>(L.g, Lc.g, L.nv, L.P64, (const double2 *)fine, b.p, nrhs, st));
   } else {
     HIPK(a.alloc(L.vsize() * nrhs));
@@ -289,7 +289,7 @@ int prolong_f64(mg_ctx *c, int level, const void *coarse, void *fine, int nrhs, 
   AsyncBuf<double2> a(st), b(st);
   HIPK(b.alloc(Lc.vsize() * nrhs));
   HIPK(pack_level(c, level + 1, coarse, b.p, nrhs, st));
-  if (level == 0) {
+  if (level == 0 && prolong_takes_mma_f64(L.g, nrhs)) {
     HIPK(prolong_fine_f64<true>(L.g, Lc.g, L.nv, L.P64, b.p, (double2 *)fine, nrhs, 0, st));
   } else {
     HIPK(a.alloc(L.vsize() * nrhs));

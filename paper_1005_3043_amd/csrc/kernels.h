@@ -203,7 +203,10 @@ hipError_t prolong_fine(const Geom &g, const Geom &gc, int nv, const S *P, const
                         int nrhs, int accumulate, hipStream_t st);
 // FP64 on the matrix cores (transfer_f64.hip): fine vectors in the fine
 // layout, or canonical arrays (CANON, [nrhs][site][12] lexicographic).
-// Aggregates of at most 256 sites, nv <= 32, any nrhs.
+// Aggregates of at most 256 sites, nv <= 32, any nrhs; where they are the faster
+// kernels:
+bool restrict_takes_mma_f64(const Geom &g, int nrhs);
+bool prolong_takes_mma_f64(const Geom &g, int nrhs);
 template <bool CANON>
 hipError_t restrict_fine_f64(const Geom &g, const Geom &gc, int nv, const double2 *P, const double2 *fine,
                              double2 *coarse, int nrhs, hipStream_t st);

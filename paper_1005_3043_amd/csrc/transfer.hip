@@ -230,9 +230,9 @@ template <typename R, typename S, typename TF>
 hipError_t restrict_fine(const Geom &g, const Geom &gc, int nv, const S *P, const TF *fine, c_t<R> *coarse,
                          int nrhs, hipStream_t st) {
   const int th = g.vb >= 256 ? 256 : (int)((g.vb + 63) / 64 * 64);
-  if constexpr (sizeof(R) == 8) {
-    if (nrhs > 1) return restrict_fine_f64<false>(g, gc, nv, P, fine, coarse, nrhs, st);
-  } else if (nrhs > 1) {
+  if constexpr (sizeof(R) == 8)
+    if (restrict_takes_mma_f64(g, nrhs)) return restrict_fine_f64<false>(g, gc, nv, P, fine, coarse, nrhs, st);
+  if (nrhs > 1) {
     hipLaunchKernelGGL((k_restrict_fine_mrhs<R, S, TF>), dim3(g.Vc, (nrhs + TR_RG - 1) / TR_RG), dim3(th), 0, st, g,
                        gc, nv, nrhs, P, fine, coarse);
     return hipGetLastError();
@@ -244,9 +244,10 @@ hipError_t restrict_fine(const Geom &g, const Geom &gc, int nv, const S *P, cons
 template <typename R, typename S>
 hipError_t prolong_fine(const Geom &g, const Geom &gc, int nv, const S *P, const c_t<R> *coarse, c_t<R> *fine,
                         int nrhs, int accumulate, hipStream_t st) {
-  if constexpr (sizeof(R) == 8) {
-    if (nrhs > 1) return prolong_fine_f64<false>(g, gc, nv, P, coarse, fine, nrhs, accumulate, st);
-  } else if (nrhs > 1) {
+  if constexpr (sizeof(R) == 8)
+    if (nrhs > 1 && prolong_takes_mma_f64(g, nrhs))
+      return prolong_fine_f64<false>(g, gc, nv, P, coarse, fine, nrhs, accumulate, st);
+  if (nrhs > 1) {
     hipLaunchKernelGGL((k_prolong_fine_mrhs<R, S>), dim3(div_up(g.V, 256), (nrhs + TR_RG - 1) / TR_RG), dim3(256), 0,
                        st, g, gc, nv, nrhs, P, coarse, fine, accumulate);
     return hipGetLastError();

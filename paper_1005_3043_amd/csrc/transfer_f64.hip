@@ -250,6 +250,26 @@ template <typename F> hipError_t groups(int nrhs, F &&f) {
 
 }  // namespace
 
+// Where the vector kernels (transfer.hip) stay: one workgroup of theirs, for
+// an aggregate and up to four right-hand sides, is done before this file's
+// chain of 16-site chunks (5 us each at Nv = 24, 3 at Nv = 8), which counts
+// while there are few workgroups; and one right-hand side leaves 15 of 16
+// matrix columns empty.  Whole calls on canonical vectors in us, this way / the
+// vector kernels with their packing, 4^4 aggregates.  Restriction of one
+// vector, Nv = 8 / 24: 8^4 50 / 87 and 32 / 41; 24^3 x 48 411 / 820 and 327 /
+// 675.  Several, Nv = 24: 16 aggregates x 2 93 / 64; 64 x 12 114 / 82; 256 x 4
+// 114 / 107; 128 x 12 116 / 171; Nv = 8: 256 x 4 64 / 58, 128 x 12 87 / 90.
+// Aggregates of 128 sites, 32 x 12, 61 / 69.
+bool restrict_takes_mma_f64(const Geom &g, int nrhs) {
+  return nrhs > 1 && (g.vb <= 128 || (uint64_t)g.Vc * nrhs > 1024);
+}
+// Prolongation, Nv = 24: one vector, 16 / 162 / 256 aggregates 60 / 67 / 84 and
+// 37 / 63 / 94; several, 64 x 12 82 / 68, 162 x 4 71 / 70, 128 x 12 84 / 121,
+// 256 x 2 89 / 95.  Aggregates of 192 sites, 32 x 1, 50 / 52.
+bool prolong_takes_mma_f64(const Geom &g, int nrhs) {
+  return g.vb <= 192 || g.Vc >= 256 || g.Vc * nrhs > 768;
+}
+
 template <bool CANON>
 hipError_t restrict_fine_f64(const Geom &g, const Geom &gc, int nv, const double2 *P, const double2 *fine,
                              double2 *coarse, int nrhs, hipStream_t st) {

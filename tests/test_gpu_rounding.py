@@ -25,7 +25,8 @@ def _context(L, block, nv):
 
 
 @pytest.mark.parametrize("L,block,nv", [((8, 8, 8, 8), (4, 4, 4, 4), 24), ((8, 8, 4, 8), (4, 4, 4, 4), 8),
-                                        ((6, 6, 4, 6), (3, 3, 2, 3), 17)])
+                                        ((6, 6, 4, 6), (3, 3, 2, 3), 17), ((8, 12, 16, 16), (4, 4, 4, 4), 24),
+                                        ((8, 12, 16, 16), (4, 4, 4, 4), 8)])
 def test_restriction(cuda, L, block, nv):
     """P^dag f sums 6 |B| complex products.  A rounding is 0.47e-16 rms of the
     partial sum it is made on, and a partial sum of a random sum is on average

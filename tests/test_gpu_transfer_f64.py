@@ -50,3 +50,31 @@ def test_vcycle_several_rhs(cuda):
     for k in range(3):
         ref = h.vcycle(r[k], 0)
         assert np.linalg.norm(z[k] - ref) <= 1e-10 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("L,nv,nrhs", [
+    ((8, 8, 16, 16), 9, (12, 13, 16, 17)),  # 64 aggregates: both lines (768 and 1024 aggregates times vectors)
+    ((12, 12, 12, 12), 17, (1, 12, 13)),    # 81: restriction's, with two row tiles
+    ((16, 16, 16, 16), 9, (1, 2, 5)),       # 256: prolongation of one vector too
+    ((8, 8, 8, 20), 32, (26,)),             # 40, the largest Nv, two groups of 13 vectors
+])
+def test_lines_between_kernels(cuda, L, nv, nrhs):
+    """4^4 aggregates, few and many of them: both sides of the lines between
+    the matrix-core and the vector kernels."""
+    import paper_1005_3043_amd as mgwd
+    block = (4, 4, 4, 4)
+    U, starts = W.gauge_field(L, 0.3, 2), W.setup_starts(L, nv, 2)
+    ctx = mgwd.MG(torch.from_numpy(U).cuda(), 0.1, [block], [nv], [torch.from_numpy(starts).cuda()], setup_rounds=0)
+    geom = tr.BlockGeometry(L, block)
+    P = ctx.export_P(0)
+    for k in nrhs:
+        psi = W.gaussian_spinor(L, k, batch=(k,))
+        F = geom.blockify(tr.fine_to_generic(psi))
+        cref = np.einsum("cxri,ncxr->ncxi", np.conj(P), F, optimize=True).reshape(k, -1)
+        c = ctx.restrict(0, torch.from_numpy(psi).cuda())
+        got = c.cpu().numpy().reshape(k, -1)
+        assert np.linalg.norm(got - cref) <= 1e-13 * np.linalg.norm(cref), k
+        fref = geom.unblockify(np.einsum("cxri,ncxi->ncxr", P, got.reshape(k, geom.Vc, 2, nv), optimize=True))
+        f = ctx.prolong(0, c).cpu().numpy().reshape(fref.shape)
+        assert np.linalg.norm(f - fref) <= 1e-13 * np.linalg.norm(fref), k
+    ctx.close()
