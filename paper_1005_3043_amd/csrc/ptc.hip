@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void k_ptc_transport_adj(Geom g, const float2 
 constexpr int WG_M = 3, WG_N = 3;
 __global__ __launch_bounds__(256, 2) void k_ptc_wgrad(Geom g, int nrow, int ncol, int ngn, const float2 *__restrict__ G,
                                                       const float2 *__restrict__ H, double2 *__restrict__ part) {
-  __shared__ float2 sh[4][64][WG_N * 4];
+  __shared__ double2 sh[4][64][WG_N * 4];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, q = lane >> 4, col = lane & 15;
   const size_t F = (size_t)12 * g.Vpad;
   const int mg = blockIdx.y / ngn * WG_M, ng = blockIdx.y % ngn * WG_N;
@@ -222,14 +222,16 @@ __global__ __launch_bounds__(256, 2) void k_ptc_wgrad(Geom g, int nrow, int ncol
     const int r = min((ng + n) * 16 + col, 4 * ncol - 1);
     hb[n] = H + (size_t)(r >> 2) * F + (size_t)(r & 3) * 3 * TILE + 4 * q;
   }
-  // Each item (16 sites of one colour) is summed by itself and then added:
-  // the rounding of one long sum over a wavefront's thousand sites made gW's
-  // error 1.4 times that of short sums added in FP64.
-  floatx4 sre[WG_M][WG_N], sim[WG_M][WG_N];
+  // Each item (16 sites of one colour) is summed by itself in FP32 and then
+  // added in FP64, so that no FP32 sum is longer than 32 products however large
+  // the lattice and however few the chunks.
+  double sre[WG_M][WG_N][4], sim[WG_M][WG_N][4];
 #pragma unroll
   for (int m = 0; m < WG_M; ++m)
 #pragma unroll
-    for (int n = 0; n < WG_N; ++n) sre[m][n] = sim[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < WG_N; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sre[m][n][v] = sim[m][n][v] = 0.0;
   // (tile, colour, 16-site block) items, dealt to the chunks' wavefronts in turn
   const uint32_t nitem = g.Vpad / TILE * 12, step = gridDim.x * 4;
   float4 an[WG_M][2], bn[WG_N][2];
@@ -266,31 +268,30 @@ __global__ __launch_bounds__(256, 2) void k_ptc_wgrad(Geom g, int nrow, int ncol
         b[n][2 * u + 1] = cf(bn[n][u].z, bn[n][u].w);
       }
     load(it + step < nitem ? it + step : it);
-    floatx4 re[WG_M][WG_N], im[WG_M][WG_N];
 #pragma unroll
-    for (int m = 0; m < WG_M; ++m)
+    for (int m = 0; m < WG_M; ++m) {
+      floatx4 re[WG_N], im[WG_N];
 #pragma unroll
-      for (int n = 0; n < WG_N; ++n) re[m][n] = im[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int n = 0; n < WG_N; ++n) re[n] = im[n] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int m = 0; m < WG_M; ++m) {
+      for (int u = 0; u < 4; ++u) {
         const float mx = -a[m][u].x;
 #pragma unroll
         for (int n = 0; n < WG_N; ++n) {
-          re[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][u].x, b[n][u].x, re[m][n], 0, 0, 0);
-          im[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][u].y, b[n][u].x, im[m][n], 0, 0, 0);
-          re[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][u].y, b[n][u].y, re[m][n], 0, 0, 0);
-          im[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(mx, b[n][u].y, im[m][n], 0, 0, 0);
+          re[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][u].x, b[n][u].x, re[n], 0, 0, 0);
+          im[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][u].y, b[n][u].x, im[n], 0, 0, 0);
+          re[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][u].y, b[n][u].y, re[n], 0, 0, 0);
+          im[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(mx, b[n][u].y, im[n], 0, 0, 0);
         }
       }
 #pragma unroll
-    for (int m = 0; m < WG_M; ++m)
+      for (int n = 0; n < WG_N; ++n)
 #pragma unroll
-      for (int n = 0; n < WG_N; ++n) {
-        sre[m][n] += re[m][n];
-        sim[m][n] += im[m][n];
-      }
+        for (int v = 0; v < 4; ++v) {
+          sre[m][n][v] += re[n][v];
+          sim[m][n][v] += im[n][v];
+        }
+    }
   }
   const int nc = 4 * ncol;
 #pragma unroll
@@ -299,14 +300,14 @@ __global__ __launch_bounds__(256, 2) void k_ptc_wgrad(Geom g, int nrow, int ncol
 #pragma unroll
     for (int n = 0; n < WG_N; ++n)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) sh[wv][lane][n * 4 + v] = cf(sre[m][n][v], sim[m][n][v]);
+      for (int v = 0; v < 4; ++v) sh[wv][lane][n * 4 + v] = make_double2(sre[m][n][v], sim[m][n][v]);
     __syncthreads();
     // wavefront v sums register v of every column tile
     for (int n = 0; n < WG_N; ++n) {
       double2 t = make_double2(0.0, 0.0);
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const float2 x = sh[w][lane][n * 4 + wv];
+        const double2 x = sh[w][lane][n * 4 + wv];
         t.x += x.x;
         t.y += x.y;
       }

@@ -114,3 +114,56 @@ def test_matrix_core_edges(cuda, L, block, nh, no, nt):
                tr.BlockGeometry(L, block).blockify(tr.fine_to_generic(Yref)).transpose(1, 2, 3, 0).reshape(-1, int(np.prod(block)) * 6, no))
     tol = max(1e-4, 1e-6 * cond)
     assert _rel(g1.cpu().numpy(), g1r) < tol and _rel(g2.cpu().numpy(), g2r) < tol
+
+
+def test_weight_gradient_rounding(cuda):
+    """Layer 2's weight gradient on 16^3 x 64 with 64 hidden channels, where
+    the site sum is dealt to the fewest wavefronts.  Unit links, hidden channel b
+    a pure hop of FP32 noise and one output equal to it keep the transported
+    fields exact, so that what is left is the rounding of the fit's residual and
+    gradient (four roundings per site, 0.7e-7) and of the sum: FP32 chains of 32
+    products, then FP64, 1.4e-7 (a rounding is 0.34e-7 rms, a chain of d products
+    0.34e-7 sqrt(d / 2)); 1.6e-7 together, the bound is twice that.  One FP32 sum
+    over a wavefront's 558 blocks of 16 sites would make 6e-7."""
+    import paper_1005_3043_amd as mgwd
+    L, nh = (16, 16, 16, 64), 64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+
+    def noise(*lead):
+        return torch.randn(*lead, L[3], L[2], L[1], L[0], 4, 3, dtype=torch.complex64, device="cuda",
+                           generator=gen).to(torch.complex128)
+
+    def hop(f, k):  # T_k with unit links, periodic
+        return f if k == 0 else torch.roll(f, 1 if (k - 1) % 2 else -1, (-3, -4, -5, -6)[(k - 1) // 2])
+
+    one = torch.eye(4, dtype=torch.complex64, device="cuda")
+    W1 = torch.zeros(nh, 1, 9, 4, 4, dtype=torch.complex64, device="cuda")
+    for b in range(nh):
+        W1[b, 0, b % 9] = one
+    W2 = torch.zeros(1, nh, 9, 4, 4, dtype=torch.complex64, device="cuda")
+    W2[0, 0, 0] = one
+    eta, V = noise(), noise(1)
+    U = torch.zeros(4, L[3], L[2], L[1], L[0], 3, 3, dtype=torch.complex128, device="cuda")
+    U[...] = torch.eye(3, device="cuda")
+    net = mgwd.PTC(L, (4, 4, 4, 4), nh, 1, t_antiperiodic=False)
+    net.set_links(U)
+    net.set_targets(V)
+    _, _, g2 = net.loss_grad(W1, W2, eta)
+
+    def blocks(f):  # [aggregate, site and component of a chirality] per chirality
+        f = f.reshape(L[3] // 4, 4, L[2] // 4, 4, L[1] // 4, 4, L[0] // 4, 4, 2, 6)
+        return f.permute(0, 2, 4, 6, 8, 1, 3, 5, 7, 9).reshape(-1, 256 * 6)
+
+    Y, T = blocks(eta), blocks(V[0])
+    C = (Y.conj() * T).sum(1) / (Y.conj() * Y).sum(1)
+    G = -2.0 / (T.abs() ** 2).sum() * (T - C[:, None] * Y) * C[:, None].conj()
+    G = G.reshape(L[3] // 4, L[2] // 4, L[1] // 4, L[0] // 4, 2, 4, 4, 4, 4, 6).permute(0, 5, 1, 6, 2, 7, 3, 8, 4, 9)
+    G = G.reshape(eta.shape).permute(4, 0, 1, 2, 3, 5).reshape(4, -1)
+    ref = torch.stack([torch.stack([
+        torch.matmul(G, hop(hop(eta, b), k).permute(4, 0, 1, 2, 3, 5).reshape(4, -1).conj().t().contiguous())
+        for k in range(9)]) for b in range(9)])
+    for b0 in range(0, 63, 9):
+        err = float((g2[0, b0:b0 + 9].to(torch.complex128) - ref).norm() / ref.norm())
+        print(f"weight gradient, channels {b0}..{b0 + 8}: {err:.2e}")
+        assert err <= 3.2e-7
