@@ -101,16 +101,16 @@ __global__ __launch_bounds__(256) void k_ptc_transport(Geom g, const float2 *__r
 // operand reads one entry of a 4x4 spin matrix, and lane (t, site) of the
 // second one entry of a spinor plane; lane (q, site) of the result holds the
 // four spins of one output channel.  A wavefront takes MIX_M row tiles (24
-// channels) of 32 sites of one colour: the fields are read once per 24 output
-// channels, the weights come from L2.  Bound by the matrix cores: 8 -> 24
+// channels at most) of 32 sites of one colour: the fields are read once per 24
+// output channels, the weights come from L2.  Bound by the matrix cores: 8 -> 24
 // channels on 16^3 x 32 is 87 GFLOP.  In vector code (each thread its site's
 // twelve components, four output channels at a time) the forward product took
 // 1.4 ms and the adjoint 1.56.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-constexpr int MIX_M = 6;   // row tiles per wavefront
-constexpr int MIX_N = 2;   // 16-site column tiles per wavefront
+constexpr int MIX_MMAX = 6;  // row tiles per wavefront at most
+constexpr int MIX_N = 2;     // 16-site column tiles per wavefront
 
-template <bool ADJ>
+template <bool ADJ, int MIX_M>
 __global__ __launch_bounds__(256, 2) void k_ptc_mix(Geom g, int nrow, int nk, int cin, const float2 *__restrict__ W,
                                                     const float2 *__restrict__ in, float2 *__restrict__ out) {
   const int lane = threadIdx.x & 63, q = lane >> 4, col = lane & 15;
@@ -197,14 +197,15 @@ __global__ __launch_bounds__(256) void k_ptc_transport_adj(Geom g, const float2 
 // Weight gradient gW[(a, s), (bk, t)] = sum over sites and colours of G_a[s][c]
 // conj(H_bk[t][c]), another complex GEMM on the FP32 matrix cores with the
 // sites as the summed index.  A wavefront holds WG_M x WG_N result tiles (12
-// channels by 12 hops) and walks its share of the 16-site blocks; lane (row,
+// channels by 12 hops at most) and walks its share of the 16-site blocks; lane (row,
 // q) reads the four consecutive sites 4 q .. 4 q + 3 of its row's plane in one
 // access and uses them in four k-steps (the sum does not depend on their
 // order).  Each of the workgroup's four wavefronts sums its own share in FP32,
 // the shares are added in FP64: part[chunk][row][column].  (One (a, bk) pair
 // per workgroup in vector code read G and H once per pair, 43 GB through L2,
 // and took 4.3 ms; this is bound by the matrix cores at 87 GFLOP.)
-constexpr int WG_M = 3, WG_N = 3;
+constexpr int WG_MMAX = 3, WG_N = 3;
+template <int WG_M>
 __global__ __launch_bounds__(256, 2) void k_ptc_wgrad(Geom g, int nrow, int ncol, int ngn, const float2 *__restrict__ G,
                                                       const float2 *__restrict__ H, double2 *__restrict__ part) {
   __shared__ double2 sh[4][64][WG_N * 4];
@@ -352,8 +353,9 @@ __global__ __launch_bounds__(256) void k_ptc_wgrad_final(int nrow, int ncol, int
 // k-steps; the four wavefronts' shares of the sum are added in LDS.  In vector
 // code from LDS rows the 24 x 48 products of 16^3 x 32 took 0.98 ms.
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-constexpr int GR_N = 3;  // column tiles per workgroup
+constexpr int GR_NMAX = 3;  // column tiles per workgroup at most
 
+template <int GR_N>
 __global__ __launch_bounds__(256) void k_fit_gram(Geom g, int ny, int nv, int ngn, const float2 *__restrict__ Y,
                                                   const float2 *__restrict__ V, double2 *__restrict__ GR) {
   __shared__ double sh[4][64][8];
@@ -635,12 +637,23 @@ hipError_t ptc_transport(const Geom &g, const float2 *U, const float2 *in, int c
   hipLaunchKernelGGL(k_ptc_transport, dim3(div_up(g.V, 256), cin), dim3(256), 0, st, g, U, in, H);
   return hipGetLastError();
 }
-// nrow output channels from nk summed ones
+// nrow output channels from nk summed ones; the row tiles in as few equal
+// groups of at most MIX_MMAX as they make.  With six always, a network of two
+// channels on 16^3 x 32 computed five empty tiles: forward pass 462 us, 301 in
+// vector code, 249 this way (24 output channels, six tiles: 1.4 ms).
 template <bool ADJ>
 static hipError_t mix(const Geom &g, int nrow, int nk, int cin, const float2 *W, const float2 *in, float2 *out,
                       hipStream_t st) {
-  const dim3 grid(div_up((long)g.Vpad / TILE * 6, 4), div_up(4 * nrow, 16 * MIX_M));
-  hipLaunchKernelGGL(k_ptc_mix<ADJ>, grid, dim3(256), 0, st, g, nrow, nk, cin, W, in, out);
+  const int tiles = div_up(4 * nrow, 16), ng = div_up(tiles, MIX_MMAX);
+  const dim3 grid(div_up((long)g.Vpad / TILE * 6, 4), ng);
+  switch (div_up(tiles, ng)) {
+#define MG_MIX(M)                                                                                              \
+  case M:                                                                                                      \
+    hipLaunchKernelGGL((k_ptc_mix<ADJ, M>), grid, dim3(256), 0, st, g, nrow, nk, cin, W, in, out);             \
+    break;
+    MG_MIX(1) MG_MIX(2) MG_MIX(3) MG_MIX(4) MG_MIX(5) MG_MIX(6)
+#undef MG_MIX
+  }
   return hipGetLastError();
 }
 hipError_t ptc_mix(const Geom &g, int cin, int cout, const float2 *W, const float2 *H, float2 *out, hipStream_t st) {
@@ -657,22 +670,42 @@ hipError_t ptc_transport_adj(const Geom &g, const float2 *U, const float2 *A, in
 // Chunks of the weight gradient's site sum: enough workgroups for the device,
 // and no more partial sums than that takes.
 int ptc_wchunks(int cin, int cout) {
-  const int groups = div_up(4 * cout, 16 * WG_M) * div_up(4 * cin * PTC_HOPS, 16 * WG_N);
+  const int groups = div_up(4 * cout, 16 * WG_MMAX) * div_up(4 * cin * PTC_HOPS, 16 * WG_N);
   return std::max(1, std::min(256, div_up(1024, groups)));
 }
 hipError_t ptc_wgrad(const Geom &g, int cin, int cout, const float2 *G, const float2 *H, double2 *part, float2 *gW,
                      hipStream_t st) {
   const int ncol = cin * PTC_HOPS, nchunk = ptc_wchunks(cin, cout);
-  const int ngm = div_up(4 * cout, 16 * WG_M), ngn = div_up(4 * ncol, 16 * WG_N);
-  hipLaunchKernelGGL(k_ptc_wgrad, dim3(nchunk, ngm * ngn), dim3(256), 0, st, g, cout, ncol, ngn, G, H, part);
+  const int tiles = div_up(4 * cout, 16), ngm = div_up(tiles, WG_MMAX), ngn = div_up(4 * ncol, 16 * WG_N);
+  const dim3 grid(nchunk, ngm * ngn);
+  // equal groups of row tiles, none of them empty: two channels on 16^3 x 32
+  // 142 us with three always, 125 in vector code, 69 this way
+  switch (div_up(tiles, ngm)) {
+#define MG_WG(M)                                                                                        \
+  case M:                                                                                               \
+    hipLaunchKernelGGL(k_ptc_wgrad<M>, grid, dim3(256), 0, st, g, cout, ncol, ngn, G, H, part);         \
+    break;
+    MG_WG(1) MG_WG(2) MG_WG(3)
+#undef MG_WG
+  }
   hipLaunchKernelGGL(k_ptc_wgrad_final, dim3(div_up(16 * cout * ncol, 32)), dim3(256), 0, st, cout, ncol, nchunk, part,
                      gW);
   return hipGetLastError();
 }
 hipError_t ptc_fit(const Geom &g, int ny, int nv, const float2 *Y, const float2 *V, const double *Z, double2 *GR,
                    double2 *C, int *flag, float2 *gY, double *part, double *loss, hipStream_t st) {
-  const int nc = ny + nv, ngn = div_up(nc, 16 * GR_N);
-  hipLaunchKernelGGL(k_fit_gram, dim3(g.Vc, 2, div_up(ny, 16) * ngn), dim3(256), 0, st, g, ny, nv, ngn, Y, V, GR);
+  const int nc = ny + nv, tiles = div_up(nc, 16), ngn = div_up(tiles, GR_NMAX);
+  const dim3 grid(g.Vc, 2, div_up(ny, 16) * ngn);
+  // equal groups again: two channels 206 us with three always, 77 in vector
+  // code, 79 this way
+  switch (div_up(tiles, ngn)) {
+#define MG_GR(N)                                                                                \
+  case N:                                                                                       \
+    hipLaunchKernelGGL(k_fit_gram<N>, grid, dim3(256), 0, st, g, ny, nv, ngn, Y, V, GR);        \
+    break;
+    MG_GR(1) MG_GR(2) MG_GR(3)
+#undef MG_GR
+  }
   hipLaunchKernelGGL(k_fit_solve, dim3(g.Vc * 2), dim3(64), sizeof(double2) * ny * nc, st, ny, nv, GR, C, flag);
   const size_t lds = sizeof(float2) * ny * (div_up(nv, 16) * 16 + 1);
   hipLaunchKernelGGL(k_fit_resid, dim3(g.Vc, 2), dim3(256), lds, st, g, ny, nv, Y, V, C, Z, gY, part);

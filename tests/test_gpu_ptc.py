@@ -167,3 +167,10 @@ def test_weight_gradient_rounding(cuda):
         err = float((g2[0, b0:b0 + 9].to(torch.complex128) - ref).norm() / ref.norm())
         print(f"weight gradient, channels {b0}..{b0 + 8}: {err:.2e}")
         assert err <= 3.2e-7
+
+
+@pytest.mark.parametrize("nh,no,nt", [(4, 12, 4), (2, 24, 24), (13, 13, 1)])
+def test_row_tile_groups(cuda, nh, no, nt):
+    """Three, six and four row tiles in one group of the mixing, one to three
+    column tiles of the Gram matrices (the other counts are above)."""
+    test_matrix_core_edges(cuda, (4, 4, 4, 4), (2, 2, 2, 2), nh, no, nt)
