@@ -133,8 +133,9 @@ struct CgFuse {
 // from b alone (e = 0): the chunked fused iteration's arithmetic with a grid
 // exchange between its phases.  words: CGP_ALL_WORDS (CGP_WORDS for sums, two
 // vectors' tagged entries of small grids behind them), and bar:
-// CGP_BAR_WORDS arrival counters, both zeroed once; epoch: advanced by more
-// than the launch's exchanges (2 maxit + 2) from one launch to the next;
+// CGP_BAR_WORDS arrival counters, both zeroed once; epoch: past the tags that
+// the words hold (a launch of it iterations makes at most 2 it + 1 exchanges
+// and as many tags from epoch + 1 on), or the words cleared;
 // launch: number of the launch on these buffers; it (two ints: iterations) and
 // fail (set when a wait gave up) are in pinned host memory.
 // Returns an error without launching when the shape does not suit the

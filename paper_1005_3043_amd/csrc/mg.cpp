@@ -844,6 +844,13 @@ int cgnr_whole(mg_ctx *c, int l, const vec_t<P> *b, vec_t<P> *e, hipStream_t st,
   Work<R> &w = work<R>(c);
   MG_TRY(c->cgp_words.alloc(CGP_ALL_WORDS));
   MG_TRY(c->cgp_bar.alloc(CGP_BAR_WORDS));
+  // The tags of a launch have to be new to the words.  They go up by the
+  // exchanges that were made, and start again from cleared words when 31 bits
+  // are used up and after a launch that gave up, whose number of exchanges is
+  // not known.
+  if (c->cgp_epoch == 0) HIPK(hipMemsetAsync(c->cgp_words, 0, sizeof(unsigned long long) * CGP_ALL_WORDS, st));
+  const unsigned epoch = c->cgp_epoch == 0 ? 1 : c->cgp_epoch;
+  c->cgp_epoch = 0;
   CgPersist<c_t<R>> a;
   a.b = b;
   a.e = e;
@@ -853,12 +860,11 @@ int cgnr_whole(mg_ctx *c, int l, const vec_t<P> *b, vec_t<P> *e, hipStream_t st,
   a.maxit = c->p.coarse_maxiter;
   a.words = c->cgp_words;
   a.bar = c->cgp_bar;
-  a.epoch = c->cgp_epoch;
+  a.epoch = epoch;
   a.launch = c->cgp_launch;
   a.it = c->h_it;
   a.fail = c->h_done;
   a.spin = c->cgp_spin;
-  c->cgp_epoch += 2u * (unsigned)a.maxit + 4u;
   c->h_done[0] = 0;
   // whole-solve CGNR classes; the FP64 solve counts as FP64 coarse stencil
   EventTimer &tw = c->tm[P::id == 2 ? 7 : P::id == 1 ? 6 : tclass<P>(true)];
@@ -891,6 +897,8 @@ int cgnr_whole(mg_ctx *c, int l, const vec_t<P> *b, vec_t<P> *e, hipStream_t st,
   }
   ran = true;
   const long it = c->h_it[0];
+  const unsigned long long next = epoch + 2ull * (unsigned)it + 2u;  // z and w per iteration, z once more
+  c->cgp_epoch = next < 1ull << 31 ? (unsigned)next : 0;
   c->n_cgnr += it;
   c->n_coarse += 1 + 2L * it;
   // in the FP32 classes the applications inside the launch are not dispatches

@@ -349,7 +349,7 @@ struct mg_ctx {
   // (level, precision class) whether the launch was refused
   mg::DevBuf<unsigned long long> cgp_words;
   mg::DevBuf<unsigned> cgp_bar;
-  unsigned cgp_epoch = 1, cgp_launch = 0;
+  unsigned cgp_epoch = 0, cgp_launch = 0;  // epoch 0: the words are to be cleared
   int cg_persist = 1;
   int gcr_fuse = 1;  // mg_set_gcr_fusion
   unsigned cgp_spin = 1u << 20;  // polls before a wait gives up

@@ -36,3 +36,28 @@ def test_exchange_forms(cuda, L, block, nv):
             assert (x1 - x0).norm() <= 1e-11 * x0.norm()
         else:
             assert torch.equal(x1, x0), prec
+
+
+@pytest.mark.parametrize("maxiter", [2**31 - 1, 2**31 - 2, 2**30])
+def test_iteration_caps_near_the_largest(cuda, maxiter):
+    """Coarse solves that follow one of a single iteration, with an iteration
+    cap of "no limit": a launch must not take the words that the one before it
+    left for its own (their tags repeated when they went up by twice the cap,
+    modulo 2^32).  Against the same solves under a cap of 100, bit for bit, on 16
+    coarse sites (tagged words)."""
+    import paper_1005_3043_amd as mgwd
+    L, block, nv = (8, 8, 8, 8), (4, 4, 4, 4), 8
+    U, starts = W.gauge_field(L, 0.3, 9), W.setup_starts(L, nv, 9)
+    g = torch.Generator().manual_seed(1)
+    b = torch.randn(3, 1, 2, 2, 2, 2, 2 * nv, dtype=torch.complex128, generator=g).cuda()
+    for prec in ("f64", "f32", "f16"):
+        out = []
+        for cap in (100, maxiter):
+            ctx = mgwd.MG(torch.from_numpy(U).cuda(), 0.1, [block], [nv], [torch.from_numpy(starts).cuda()],
+                          setup_rounds=1, coarse_tol=0.95, coarse_maxiter=cap)
+            ctx.set_coarse_variant(0)
+            out.append([ctx.coarse_solve(b[k], prec) for k in (0, 1, 2, 0, 1)])
+            ctx.close()
+        assert all(it == [1] for _, it in out[0]), [it for _, it in out[0]]
+        for (x0, i0), (x1, i1) in zip(*out):
+            assert i0 == i1 and torch.equal(x0, x1), prec
