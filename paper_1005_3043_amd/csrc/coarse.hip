@@ -534,7 +534,7 @@ __device__ __forceinline__ bool cgp_gather(const unsigned long long *words, unsi
       for (;;) {
         unsigned c = __hip_atomic_load(bar + lane * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         c = wave_sum(c);
-        if (c >= target) break;
+        if ((int)(c - target) >= 0) break;  // (both modulo 2^32)
         if (++spins > spin_max) {
           if (lane == 0) {
             *bad = 1;

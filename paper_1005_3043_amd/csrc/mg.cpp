@@ -942,7 +942,7 @@ template <typename P> int cgnr(mg_ctx *c, int l, const vec_t<P> *b, vec_t<P> *e,
   if (!fused) HIPK(copy<R>(w.cp, w.cz, n * nrhs, st));
   // Captured chunks (not with timing on: event records cannot be captured)
   ChunkGraph *gph = (c->use_graph && !c->timing) ? chunk_graph<P>(c, l, e, nrhs, var, fused, st) : nullptr;
-  const int nchunks = (c->p.coarse_maxiter + CG_CHUNK - 1) / CG_CHUNK;
+  const int nchunks = (c->p.coarse_maxiter - 1) / CG_CHUNK + 1;
   c->n_coarse_disp += nrhs;  // the initial application above
   int last = 0;
   for (int ch = 0; ch < nchunks; ++ch) {

@@ -61,3 +61,24 @@ def test_iteration_caps_near_the_largest(cuda, maxiter):
         assert all(it == [1] for _, it in out[0]), [it for _, it in out[0]]
         for (x0, i0), (x1, i1) in zip(*out):
             assert i0 == i1 and torch.equal(x0, x1), prec
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+def test_chunks_under_the_largest_cap(cuda, prec):
+    """The number of chunks under a cap of 2^31 - 1 (it overflowed, no chunk
+    ran and the solution was zero), one and three right-hand sides."""
+    import paper_1005_3043_amd as mgwd
+    L, block, nv = (8, 8, 8, 8), (4, 4, 4, 4), 8
+    U, starts = W.gauge_field(L, 0.3, 9), W.setup_starts(L, nv, 9)
+    g = torch.Generator().manual_seed(2)
+    b = torch.randn(3, 2, 2, 2, 2, 2 * nv, dtype=torch.complex128, generator=g).cuda()
+    out = []
+    for cap in (100, 2**31 - 1):
+        ctx = mgwd.MG(torch.from_numpy(U).cuda(), 0.1, [block], [nv], [torch.from_numpy(starts).cuda()],
+                      setup_rounds=1, coarse_maxiter=cap, max_rhs=3)
+        ctx.set_coarse_variant(0)
+        ctx.set_cgnr_persistent(False)
+        out.append([ctx.coarse_solve(b[:k], prec) for k in (1, 3)])
+        ctx.close()
+    for (x0, i0), (x1, i1) in zip(*out):
+        assert i0 == i1 and min(i0) > 2 and torch.equal(x0, x1)
