@@ -18,9 +18,9 @@
 //
 // Per site the hops are added in the order of k_dslash and with its hop code,
 // so every precision gives k_dslash's bits on the same rounded inputs.
-#include <cmath>
 #include <type_traits>
 
+#include "canon_order.h"
 #include "kernels.h"
 #include "wilson_site.h"
 
@@ -37,7 +37,7 @@ struct CanonGeom {
   uint32_t V, ntile;
   FastDiv f[3];
   int antiperiodic;
-  uint32_t h;  // extent of the visiting order's blocks in y, z and t
+  CanonOrder order;  // of the streaming form
 };
 
 typedef double double2v __attribute__((ext_vector_type(2)));
@@ -125,27 +125,6 @@ __device__ __forceinline__ uint32_t xcd_share(uint32_t bid, uint32_t n) {
   return k * q + (k < rem ? k : rem) + (bid >> 3);
 }
 
-// Site n of the streaming form's visiting order: blocks of L_x * h * h * h
-// sites (cut short at the far edges), x fastest inside a block and the blocks
-// t fastest, then z, then y.  The sites that an XCD has in flight then form a
-// compact block instead of a run of planes, and most neighbours come from its
-// own L2: see visit_extent.
-__device__ __forceinline__ uint32_t site_at(const CanonGeom &g, uint32_t n) {
-  const uint32_t L0 = (uint32_t)g.L[0], L1 = (uint32_t)g.L[1], L2 = (uint32_t)g.L[2], L3 = (uint32_t)g.L[3];
-  uint32_t per = L0 * L2 * L3 * g.h;
-  const uint32_t Y = n / per * g.h, hy = min(g.h, L1 - Y);
-  n -= Y * L0 * L2 * L3;
-  per = L0 * hy * L3 * g.h;
-  const uint32_t Z = n / per * g.h, hz = min(g.h, L2 - Z);
-  n -= Z * L0 * hy * L3;
-  const uint32_t area = L0 * hy * hz, t = n / area;  // whole time slices of the column: blocks in t need no split
-  n -= t * area;
-  const uint32_t z = n / (L0 * hy);
-  n -= z * L0 * hy;
-  const uint32_t y = n / L0;
-  return n - y * L0 + g.S[1] * (Y + y) + g.S[2] * (Z + z) + g.S[3] * t;
-}
-
 template <typename C> __device__ __forceinline__ void store_flat(double2 *out, size_t at, C v) {
   const double2v d = {(double)v.x, (double)v.y};
   __builtin_nontemporal_store(d, reinterpret_cast<double2v *>(out + at));
@@ -182,7 +161,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_canon(CanonGeom g, const doub
   }
   const bool live = rhs < (uint32_t)nrhs;
   const double2 *vin = in + (size_t)(live ? rhs : nrhs - 1) * 12 * g.V;
-  const uint32_t n0 = tile * 64, s = site_at(g, min(n0 + lane, g.V - 1));
+  const uint32_t n0 = tile * 64, s = site_at(g.order, min(n0 + lane, g.V - 1));
   int x[4];
   coords_of(g, s, x);
 #pragma unroll
@@ -403,17 +382,6 @@ __global__ __launch_bounds__(512) void k_dslash_canon_split(CanonGeom g, const d
   }
 }
 
-// Extent h of the visiting order's blocks: one time slice of a column of
-// blocks (L_x h h sites of links and spinors) takes about 1.5 MB, so that the
-// three slices the stencil spans fit an XCD's 4 MB L2 with what is in flight.
-// On 32^3 x 64: FP32 x 12 right-hand sides 4.60 / 3.80 / 4.15 ms with h = 2 /
-// 4 / 8 (planes walked whole: 5.09 ms, 38 GB fetched), FP64 x 1 669 / 583 /
-// 540 us.
-inline uint32_t visit_extent(int Lx, int nrhs) {
-  const double h = std::sqrt(1.5e6 / ((double)Lx * (192.0 * nrhs + 576.0)));
-  return h < 2.83 ? 2u : h < 5.66 ? 4u : h < 11.3 ? 8u : 16u;  // nearest power of two: lattices come in those
-}
-
 // Up to this many tiles times right-hand sides the latency form is taken: two
 // of its workgroups per CU at most, all resident at once.  7 x 10 x 13 x 18
 // with five right-hand sides (1 280): 16.3 us streaming, 19.3 us this way;
@@ -432,7 +400,7 @@ hipError_t launch(const CanonGeom &g0, const double2 *U, const double2 *in, doub
                        (R)diag);
     return hipGetLastError();
   }
-  g.h = visit_extent(g.L[0], nrhs);
+  g.order = canon_order(g.L, nrhs);
   if (nrhs == 1) {
     const int nw = 4;
     const uint32_t nblk = (g.ntile + nw - 1) / nw;
