@@ -344,8 +344,10 @@ int mg_coarse_variant(mg_ctx_t *ctx, int level, mg_prec_t prec, int nrhs,
  * launch that keeps each coarse site's operator rows in registers and joins
  * its two stencil phases per iteration with grid-wide exchanges; off, they
  * run as chunks of captured per-iteration launches.
- * Both forms do the same arithmetic in the same order (same iterates, same
- * iteration counts).  Where the device cannot hold the whole coarse grid at
+ * Both forms do the iterations' arithmetic in the same order in every class:
+ * the same iterates, bit for bit.  Only ||b|| is summed in another order, so
+ * that a residual within a rounding of coarse_tol ||b|| may end one form an
+ * iteration before the other.  Where the device cannot hold the whole coarse grid at
  * once (or the operator rows do not fit), the chunks run regardless.  A
  * wait gives up after 2^20 polls (on >= 2: after `on` polls, to
  * exercise this path); the launch then leaves, and that coarsest solve is

@@ -77,6 +77,14 @@ __device__ __forceinline__ uint32_t slot_site(const Geom &g, uint32_t s, int slo
   }
 }
 
+// |v|^2 with the roundings written out: left to the compiler they differ from
+// kernel to kernel, and the CGNR's two forms in FP64 with them (in the FP32
+// classes the products are exact).
+template <typename C> __device__ __forceinline__ double norm2_of(C v) {
+  const double x = v.x, y = v.y;
+  return fma(x, x, y * y);
+}
+
 // Sums of up to three partial arrays over the workgroup in one pass: out[0]
 // = sum a[0..na), out[1] = sum b[0..nb), out[2] = sum c[0..nb) (NULL arrays
 // give 0).  Fixed order; result in every thread.
@@ -242,7 +250,7 @@ __global__ __launch_bounds__(512) void k_coarse(Geom g, int n, const S *__restri
           C *e = reinterpret_cast<C *>(fz.e) + rhs_off;
           const C *pp = reinterpret_cast<const C *>(fz.p) + rhs_off;
           e[o] = cfma(mk<C>(coef, 0), pp[o], e[o]);
-          own_sq += (double)v.x * v.x + (double)v.y * v.y;
+          own_sq += norm2_of(v);
         }
       }
       if (dagger && j >= (n >> 1)) v = mk<C>(-v.x, -v.y);
@@ -299,7 +307,7 @@ __global__ __launch_bounds__(512) void k_coarse(Geom g, int n, const S *__restri
     const C c = vin[row];
     t[0] = (double)sum.x * c.x + (double)sum.y * c.y;
     t[1] = (double)sum.x * c.y - (double)sum.y * c.x;
-    t[2] = (double)sum.x * sum.x + (double)sum.y * sum.y;
+    t[2] = norm2_of(sum);
   }
   if (partials != nullptr || fz.kind == 2) {
     double v4[4] = {t[0], t[1], t[2], own_sq};
@@ -677,7 +685,7 @@ __global__ __launch_bounds__(512, DIRECT || (sizeof(S) == 16 && PM == 16) ? 2 : 
       ploc[i1] = mk<C>(0, 0);
       vin[i1] = neg1 ? mk<C>(-b1.x, -b1.y) : b1;
     }
-    if (tid < n) sq = (double)b0.x * b0.x + (double)b0.y * b0.y;
+    if (tid < n) sq = norm2_of(b0);
   }
   C e = mk<C>(0, 0), x0 = e, x1 = e;
   // the entries of z (which 0) and w (1): tagged words, or the arrays themselves
@@ -710,7 +718,7 @@ __global__ __launch_bounds__(512, DIRECT || (sizeof(S) == 16 && PM == 16) ? 2 : 
       if (tid < n) {
         if (tid >= half) zv = mk<C>(-zv.x, -zv.y);
         put(a.z, 0, zv, phase + 1);
-        v[0] = (double)zv.x * zv.x + (double)zv.y * zv.y;
+        v[0] = norm2_of(zv);
       }
       ++phase;
       cgp_announce<DIRECT>(v, a.words, bar, nblk, a.epoch + phase);
@@ -743,7 +751,7 @@ __global__ __launch_bounds__(512, DIRECT || (sizeof(S) == 16 && PM == 16) ? 2 : 
       double v[2] = {0.0, 0.0};
       if (tid < n) {
         put(a.w, 1, wv, phase + 1);
-        v[0] = (double)wv.x * wv.x + (double)wv.y * wv.y;
+        v[0] = norm2_of(wv);
       }
       ++phase;
       cgp_announce<DIRECT>(v, a.words, bar, nblk, a.epoch + phase);
@@ -764,7 +772,7 @@ __global__ __launch_bounds__(512, DIRECT || (sizeof(S) == 16 && PM == 16) ? 2 : 
       vin[i0] = neg0 ? mk<C>(-v.x, -v.y) : v;
       if (tid < n) {
         e = cfma(mk<C>(alpha, 0), ploc[tid], e);
-        sq = (double)v.x * v.x + (double)v.y * v.y;
+        sq = norm2_of(v);
       }
     }
     if (h1) {

@@ -829,8 +829,8 @@ ChunkGraph *chunk_graph(mg_ctx *c, int l, vec_t<P> *e, int nrhs, int var, bool f
   return g;
 }
 
-// The fused CGNR of one right-hand side as one cooperative launch (same
-// arithmetic and iteration count as the chunked path).  ran = false, and
+// The fused CGNR of one right-hand side as one cooperative launch (the iterates
+// of the chunked path; ||b|| is summed in another order).  ran = false, and
 // nothing is launched, when the shape or the device cannot take it, or when
 // a wait in it gave up; the caller then runs the chunks.
 template <typename P>

@@ -82,3 +82,40 @@ def test_chunks_under_the_largest_cap(cuda, prec):
         ctx.close()
     for (x0, i0), (x1, i1) in zip(*out):
         assert i0 == i1 and min(i0) > 2 and torch.equal(x0, x1)
+
+
+@pytest.mark.parametrize("L,block,nv", [((4, 4, 4, 4), (2, 2, 2, 2), 3), ((8, 8, 8, 8), (2, 2, 2, 4), 5),
+                                        ((8, 8, 6, 6), (2, 2, 2, 2), 5), ((8, 8, 8, 16), (2, 2, 2, 2), 4)])
+def test_whole_solve_runs_and_equals_the_chunks(cuda, L, block, nv):
+    """In every precision class, FP64 too, the whole-solve launch ran (one timed
+    launch per coarsest solve and no fallback; chunks take two per iteration)
+    and its iterates are those of the chunks, bit for bit; 16, 128, 144 and 512
+    coarse sites."""
+    import paper_1005_3043_amd as mgwd
+    U, starts = W.gauge_field(L, 0.3, 9), W.setup_starts(L, nv, 9)
+    ctx = mgwd.MG(torch.from_numpy(U).cuda(), 0.1, [block], [nv], [torch.from_numpy(starts).cuda()], setup_rounds=1)
+    ctx.set_coarse_variant(0)
+    ctx.set_timing(True)
+    g = torch.Generator().manual_seed(3)
+    b = torch.randn(1, *(L[3 - k] // block[3 - k] for k in range(4)), 2 * nv, dtype=torch.complex128, generator=g)
+    b = b.cuda()
+    f = torch.randn(L[3], L[2], L[1], L[0], 4, 3, dtype=torch.complex128, generator=g).cuda()
+    for prec, name in (("f64", "coarse_f64"), ("f32", "cgnr_f32"), ("f16", "cgnr_f16")):
+        ctx.set_precond_prec(prec)
+        out = {}
+        for on in (True, False):
+            ctx.set_cgnr_persistent(on)
+            x, it = ctx.coarse_solve(b, prec)
+            _, info, _ = ctx.solve(f, 1e-8)
+            assert info["n_cgnr_fallbacks"] == 0
+            launches = info["kernels"][name]["launches"]
+            if on:
+                assert launches == info["n_vcycles"], (prec, launches)
+            elif prec == "f64":
+                assert launches >= 2 * info["n_cgnr_iters"], launches
+            else:
+                assert launches == 0
+            out[on] = (x, it, info["iters"][0], info["n_cgnr_iters"])
+        assert out[True][1:] == out[False][1:] and out[True][1][0] > 3, prec
+        assert torch.equal(out[True][0], out[False][0]), prec
+    ctx.close()
