@@ -119,3 +119,51 @@ def test_whole_solve_runs_and_equals_the_chunks(cuda, L, block, nv):
         assert out[True][1:] == out[False][1:] and out[True][1][0] > 3, prec
         assert torch.equal(out[True][0], out[False][0]), prec
     ctx.close()
+
+
+def test_refused_shape_takes_the_chunks(cuda):
+    """n = 40 in FP64 needs 30 operator entries per thread, more than the launch
+    keeps in registers: chunks, without a fallback being counted; the FP32
+    classes run the launch on the same 64 coarse sites."""
+    import paper_1005_3043_amd as mgwd
+    L, block, nv = (8, 8, 8, 8), (2, 2, 4, 4), 20
+    U, starts = W.gauge_field(L, 0.3, 9), W.setup_starts(L, nv, 9)
+    ctx = mgwd.MG(torch.from_numpy(U).cuda(), 0.1, [block], [nv], [torch.from_numpy(starts).cuda()], setup_rounds=1)
+    ctx.set_coarse_variant(0)
+    ctx.set_timing(True)
+    f = torch.from_numpy(W.gaussian_spinor(L, 1)).cuda()
+    for prec, name in (("f64", "coarse_f64"), ("f32", "cgnr_f32"), ("f16", "cgnr_f16")):
+        ctx.set_precond_prec(prec)
+        _, info, rc = ctx.solve(f, 1e-8)
+        assert rc == 0 and info["n_cgnr_fallbacks"] == 0
+        launches = info["kernels"][name]["launches"]
+        if prec == "f64":
+            assert launches >= 2 * info["n_cgnr_iters"], launches
+        else:
+            assert launches == info["n_vcycles"], (prec, launches)
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_tagged_words_give_up_cleanly(cuda, prec):
+    """A wait limited to two polls on 128 coarse sites, where the words are
+    tagged: the launch gives up (every wait is bounded, so all workgroups leave),
+    the chunks solve again from the right-hand side, and later launches, whose
+    words start cleared, are right again."""
+    import paper_1005_3043_amd as mgwd
+    L, block, nv = (8, 8, 8, 8), (2, 2, 2, 4), 5
+    U, starts = W.gauge_field(L, 0.3, 9), W.setup_starts(L, nv, 9)
+    ctx = mgwd.MG(torch.from_numpy(U).cuda(), 0.1, [block], [nv], [torch.from_numpy(starts).cuda()], setup_rounds=1,
+                  precond_prec=prec)
+    ctx.set_coarse_variant(0)
+    f = torch.from_numpy(W.gaussian_spinor(L, 1)).cuda()
+    out = []
+    for on, polls in ((True, 2), (False, None), (True, None)):
+        ctx.set_cgnr_persistent(on, polls=polls)
+        x, info, rc = ctx.solve(f, 1e-10)
+        out.append((x.clone(), info["iters"], info["n_cgnr_iters"], info["n_cgnr_fallbacks"], rc))
+    ctx.close()
+    print(f"{prec}: fallbacks {[o[3] for o in out]}")
+    assert out[0][3] >= 1 and out[1][3] == out[2][3] == 0
+    for o in out:
+        assert o[4] == 0 and o[1:3] == out[1][1:3] and torch.equal(o[0], out[1][0])
