@@ -454,91 +454,57 @@ static bool take_split(const Geom &g, int nrhs) {
 int dslash_blocks(const Geom &g) { return div_up(g.V, 256); }
 int dslash_partials(const Geom &g, int nrhs) { return take_split(g, nrhs) ? div_up(g.V, 64) : dslash_blocks(g); }
 
+// Modes that exist for a pair of storage types: FP64 arithmetic on FP32
+// spinors is only applied plainly (dslash_in32), a binary16 output of FP32
+// spinors is only the residual, the q recursion is not taken in FP64.
+template <typename R, typename TI, typename TO> constexpr bool has_mode(DslashMode m) {
+  if (!std::is_same<TI, TO>::value) return m == (sizeof(R) == 8 ? DS_PLAIN : DS_RESID);
+  return m != DS_MRQ || sizeof(R) == 4;
+}
+// f(constant mode)
+template <typename R, typename TI, typename TO, typename F> static hipError_t with_mode(DslashMode mode, F &&f) {
+  switch (mode) {
+#define MG_MODE(M)                                         \
+  case M:                                                  \
+    if constexpr (has_mode<R, TI, TO>(M)) {                \
+      f(std::integral_constant<int, M>());                 \
+      return hipGetLastError();                            \
+    }                                                      \
+    break;
+    MG_MODE(DS_PLAIN) MG_MODE(DS_RESID) MG_MODE(DS_MR) MG_MODE(DS_MRQ)
+#undef MG_MODE
+  }
+  return hipErrorInvalidValue;
+}
+
 template <typename R, int NL, typename S, int K, typename TI, typename TO>
 static hipError_t launch_rb(const Geom &g, const S *U, const TI *in, TO *out, const TO *b, double diag, int nrhs,
                             DslashMode mode, double *partials, hipStream_t st, MrqArgs<TO> mq) {
-  dim3 grid(dslash_blocks(g), (nrhs + K - 1) / K);
-  switch (mode) {
-    case DS_PLAIN:
-      hipLaunchKernelGGL((k_dslash_rb<R, DS_PLAIN, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                         (R)diag, partials, nrhs, mq);
-      break;
-    case DS_RESID:
-      hipLaunchKernelGGL((k_dslash_rb<R, DS_RESID, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                         (R)diag, partials, nrhs, mq);
-      break;
-    case DS_MR:
-      hipLaunchKernelGGL((k_dslash_rb<R, DS_MR, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                         (R)diag, partials, nrhs, mq);
-      break;
-    case DS_MRQ:
-      if constexpr (std::is_same<TI, TO>::value && sizeof(R) == 4)
-        hipLaunchKernelGGL((k_dslash_rb<R, DS_MRQ, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b,
-                           (R)diag, partials, nrhs, mq);
-      else
-        return hipErrorInvalidValue;
-      break;
-  }
-  return hipGetLastError();
+  const dim3 grid(dslash_blocks(g), (nrhs + K - 1) / K);
+  return with_mode<R, TI, TO>(mode, [&](auto m) {
+    hipLaunchKernelGGL((k_dslash_rb<R, decltype(m)::value, NL, S, K, TI, TO>), grid, dim3(256), 0, st, g, U, in, out,
+                       b, (R)diag, partials, nrhs, mq);
+  });
 }
 
 template <typename R, int NL, typename S, typename TI, typename TO>
 static hipError_t launch(const Geom &g, const S *U, const TI *in, TO *out, const TO *b, double diag, int nrhs,
                          DslashMode mode, double *partials, hipStream_t st, MrqArgs<TO> mq) {
-  if (take_split(g, nrhs)) {
-    dim3 grid(div_up(g.V, 64), nrhs);
-    switch (mode) {
-      case DS_PLAIN:
-        hipLaunchKernelGGL((k_dslash_split<R, DS_PLAIN, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
-                           (R)diag, partials, mq);
-        break;
-      case DS_RESID:
-        hipLaunchKernelGGL((k_dslash_split<R, DS_RESID, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
-                           (R)diag, partials, mq);
-        break;
-      case DS_MR:
-        hipLaunchKernelGGL((k_dslash_split<R, DS_MR, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
-                           (R)diag, partials, mq);
-        break;
-      case DS_MRQ:
-        if constexpr (std::is_same<TI, TO>::value && sizeof(R) == 4)
-          hipLaunchKernelGGL((k_dslash_split<R, DS_MRQ, NL, S, TI, TO>), grid, dim3(512), 0, st, g, U, in, out, b,
-                             (R)diag, partials, mq);
-        else
-          return hipErrorInvalidValue;
-        break;
-    }
-    return hipGetLastError();
-  }
+  if (take_split(g, nrhs))
+    return with_mode<R, TI, TO>(mode, [&](auto m) {
+      hipLaunchKernelGGL((k_dslash_split<R, decltype(m)::value, NL, S, TI, TO>), dim3(div_up(g.V, 64), nrhs),
+                         dim3(512), 0, st, g, U, in, out, b, (R)diag, partials, mq);
+    });
   if (nrhs > 1) {
     if constexpr (!(sizeof(R) == 8 && std::is_same<TI, double2>::value))
       if (take_three<R, TI>(nrhs))
         return launch_rb<R, NL, S, 3>(g, U, in, out, b, diag, nrhs, mode, partials, st, mq);
     return launch_rb<R, NL, S, 2>(g, U, in, out, b, diag, nrhs, mode, partials, st, mq);
   }
-  dim3 grid(dslash_blocks(g), nrhs);
-  switch (mode) {
-    case DS_PLAIN:
-      hipLaunchKernelGGL((k_dslash<R, DS_PLAIN, NL, S, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b, (R)diag,
-                         partials, mq);
-      break;
-    case DS_RESID:
-      hipLaunchKernelGGL((k_dslash<R, DS_RESID, NL, S, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b, (R)diag,
-                         partials, mq);
-      break;
-    case DS_MR:
-      hipLaunchKernelGGL((k_dslash<R, DS_MR, NL, S, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b, (R)diag,
-                         partials, mq);
-      break;
-    case DS_MRQ:
-      if constexpr (std::is_same<TI, TO>::value && sizeof(R) == 4)
-        hipLaunchKernelGGL((k_dslash<R, DS_MRQ, NL, S, TI, TO>), grid, dim3(256), 0, st, g, U, in, out, b, (R)diag,
-                           partials, mq);
-      else
-        return hipErrorInvalidValue;
-      break;
-  }
-  return hipGetLastError();
+  return with_mode<R, TI, TO>(mode, [&](auto m) {
+    hipLaunchKernelGGL((k_dslash<R, decltype(m)::value, NL, S, TI, TO>), dim3(dslash_blocks(g), nrhs), dim3(256), 0,
+                       st, g, U, in, out, b, (R)diag, partials, mq);
+  });
 }
 
 template <typename R, typename S, typename TI, typename TO>
