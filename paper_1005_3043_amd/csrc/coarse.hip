@@ -1268,6 +1268,10 @@ static size_t mma_lds_bytes(int n, int nrhs, int ks) {
   return b > r ? b : r;
 }
 
+// Which products the variants take.  The bound on the staged vectors leaves a
+// workgroup at most 72 KB of the CU's 160 KB of LDS: n = 64 with 12 right-hand
+// sides on eight wavefronts, 64 KB of sums (60 KB of vectors before them) and 6
+// KB of partial products.
 bool coarse_mma_ok(int n, int nrhs, int variant) {
   const int ks = variant & 7;
   if (n > COARSE_NMAX || nrhs < 1 || nrhs > MMA_NR) return false;
