@@ -160,10 +160,11 @@ typedef struct {
   int n_coarse_apply;           /* coarse stencil applications, all levels   */
   int n_coarse_dispatch;        /* coarse stencil applications dispatched,
                                    including those that returned at once
-                                   because their RHS had converged (those
-                                   inside a whole-solve CGNR launch of the
-                                   FP32 classes are applications, not
-                                   dispatches)                            */
+                                   because their RHS had converged.  Those
+                                   inside a whole-solve CGNR launch are
+                                   counted in FP64, as when the chunks
+                                   dispatched each, but not in the FP32
+                                   classes                                */
   int n_cgnr_iters;             /* coarsest CGNR iterations, summed          */
   int n_vcycles;                /* preconditioner applications               */
   double t_setup_s, t_solve_s;  /* wall time of the last setup / solve       */
@@ -175,7 +176,8 @@ typedef struct {
    * their right-hand side had converged.  Classes 6 and 7: the whole-solve
    * coarsest CGNR launches (mg_set_cgnr_persistent) with the FP32 and the
    * FP16-stored operator, one launch per coarsest solve, sites = coarse
-   * sites x stencil applications inside the launches.  Classes 8 and 9:
+   * sites x stencil applications inside the launches (the FP64 ones count
+   * like that in class 1, beside its single applications).  Classes 8 and 9:
    * the fine stencil launches of the MR steps taken by the q recursion
    * (each also reads the previous residual and writes the next one) in
    * the FP32 and FP16 classes; class 2 and 4 count the other fine-stencil
@@ -196,7 +198,8 @@ typedef struct {
  * FP32; FP32 arithmetic; the input is rounded to FP32, then to binary16, so
  * every stored entry carries a relative rounding of up to 2^-11).  Inputs
  * and outputs stay complex128.  Stateless: one kernel on the canonical
- * arrays, no memory of its own.                                          */
+ * arrays, no memory of its own (but a temporary where out overlaps U or a
+ * part of in).                                                           */
 int wilson_apply(const mg_lattice_t *lat, const void *U, double mass,
                  const void *in, void *out, int nrhs, mg_prec_t prec,
                  hipStream_t stream);

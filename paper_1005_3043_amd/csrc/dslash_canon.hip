@@ -7,14 +7,16 @@
 // (input) packing, 0.55 stencil and 0.39 unpacking, and each call allocated
 // and freed the copies.
 //
-// Bound by memory.  A site's 12 spinor components (192 bytes) and 9 link
-// entries (144 bytes) are contiguous, which one thread per site would read in
-// strides; instead a wavefront reads the entries of its 64 consecutive sites
-// (or of their neighbours, contiguous up to the lattice's edges) as one flat
-// run, 1 KiB per load, and hands them to the threads through LDS, rounded to
-// the arithmetic type on the way.  Rows of 13 spinor and 9 link entries make
-// the per-thread reads free of bank conflicts (an odd number of 8- or 16-byte
-// units).  The output leaves the same way.
+// Bound by memory (32^3 x 64, FP64 x 1 and FP32 x 12: 7.1 to 7.4 TB/s of reads
+// past L2 and writes), in the binary16 class by the vector units' rounding and
+// conversions (24^3 x 48 x 12: at least 68 % busy).  A site's 12 spinor
+// components (192 bytes) and 9 link entries (144 bytes) are contiguous, which
+// one thread per site would read in strides; instead a wavefront reads the
+// entries of its 64 consecutive sites (or of their neighbours, contiguous up to
+// the lattice's edges) as one flat run, 1 KiB per load, and hands them to the
+// threads through LDS, rounded to the arithmetic type on the way.  Rows of 13
+// spinor and 9 link entries make the per-thread reads free of bank conflicts
+// (an odd number of 8- or 16-byte units).  The output leaves the same way.
 //
 // Per site the hops are added in the order of k_dslash and with its hop code,
 // so every precision gives k_dslash's bits on the same rounded inputs.

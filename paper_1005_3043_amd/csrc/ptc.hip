@@ -103,7 +103,8 @@ __global__ __launch_bounds__(256) void k_ptc_transport(Geom g, const float2 *__r
 // four spins of one output channel.  A wavefront takes MIX_M row tiles (24
 // channels at most) of 32 sites of one colour: the fields are read once per 24
 // output channels, the weights come from L2.  Bound by the matrix cores: 8 -> 24
-// channels on 16^3 x 32 is 87 GFLOP.  In vector code (each thread its site's
+// channels on 16^3 x 32 is 87 GFLOP, 0.80 and 0.88 ms with them 72 and 64 %
+// busy and 1.2 and 1.8 GB moved.  In vector code (each thread its site's
 // twelve components, four output channels at a time) the forward product took
 // 1.4 ms and the adjoint 1.56.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -203,7 +204,8 @@ __global__ __launch_bounds__(256) void k_ptc_transport_adj(Geom g, const float2 
 // order).  Each of the workgroup's four wavefronts sums its own share in FP32,
 // the shares are added in FP64: part[chunk][row][column].  (One (a, bk) pair
 // per workgroup in vector code read G and H once per pair, 43 GB through L2,
-// and took 4.3 ms; this is bound by the matrix cores at 87 GFLOP.)
+// and took 4.3 ms; this takes 0.95 for 8 -> 24 channels on 16^3 x 32, 87 GFLOP
+// with the matrix cores 59 % busy and 3.6 GB fetched.)
 constexpr int WG_MMAX = 3, WG_N = 3;
 template <int WG_M>
 __global__ __launch_bounds__(256, 2) void k_ptc_wgrad(Geom g, int nrow, int ncol, int ngn, const float2 *__restrict__ G,
